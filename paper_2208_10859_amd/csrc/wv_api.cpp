@@ -93,7 +93,11 @@ wv_status wv_create(wv_ctx** out, const wv_desc* desc) {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device);
   if (e == hipSuccess) e = hipMalloc((void**)&c->counter, 2 * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->counter, 0, 2 * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipHostMalloc((void**)&c->tab_host, kTableSlots * kTableBytes, hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&c->tab_host, kTableSlots * kTableBytes + sizeof(int), hipHostMallocDefault);
+  if (e == hipSuccess) {
+    c->enc_flag = (int*)(c->tab_host + kTableSlots * kTableBytes);
+    *c->enc_flag = 0;
+  }
   if (e == hipSuccess) e = hipMalloc((void**)&c->tab_dev, kTableSlots * kTableBytes);
   for (int i = 0; e == hipSuccess && i < kTableSlots; ++i)
     e = hipEventCreateWithFlags(&c->tab_done[i], hipEventDisableTiming);
@@ -122,6 +126,7 @@ wv_status wv_destroy(wv_ctx* c) {
   hipDeviceSynchronize();
   if (c->counter) hipFree(c->counter);
   if (c->plain_ws) hipFree(c->plain_ws);
+  if (c->enc_ws) hipFree(c->enc_ws);
   if (c->tab_dev) hipFree(c->tab_dev);
   if (c->tab_host) hipHostFree(c->tab_host);
   for (int i = 0; i < kTableSlots; ++i)
@@ -538,24 +543,22 @@ extern "C" wv_status wv_encode_intra(wv_ctx* c, const void* const* src, void* co
   if (qstep < 1 || qstep > 65535) return fail(WV_EINVAL, "qstep %d outside 1..65535", qstep);
   for (int p = 0; p < c->nplanes; ++p)
     if (!src[p] || !coeffs[p]) return fail(WV_EINVAL, "plane %d pointer is NULL", p);
-  const size_t vbytes = c->d.wavelet == WV_W53 ? 4 : 8;
-  const size_t bytes = (size_t)c->n_tiles * c->d.tile * c->d.tile * vbytes;
-  void* ws = nullptr;
-  int* flag = nullptr;
-  hipError_t e = hipMalloc(&ws, bytes);
-  if (e != hipSuccess) return fail(WV_ENOMEM, "encoder workspace: %s", hipGetErrorString(e));
-  e = hipMalloc((void**)&flag, sizeof(int));
-  if (e == hipSuccess) e = hipMemsetAsync(flag, 0, sizeof(int), s);
-  if (e == hipSuccess)
-    e = launch_encode(c->d.wavelet, c->nplanes, c->n_tiles, c->d.tile, c->d.levels, qstep, src,
-                      coeffs, ws, flag, s);
-  int h_flag = 0;
-  if (e == hipSuccess) e = hipMemcpyAsync(&h_flag, flag, sizeof(int), hipMemcpyDeviceToHost, s);
+  const size_t bytes = encode_workspace_bytes(c->d.wavelet, c->nplanes, c->n_tiles, c->d.tile, c->d.levels);
+  if (bytes && !c->enc_ws) {
+    const hipError_t e = hipMalloc(&c->enc_ws, bytes);
+    if (e != hipSuccess) {
+      c->enc_ws = nullptr;
+      return fail(WV_ENOMEM, "encoder workspace: %s", hipGetErrorString(e));
+    }
+  }
+  hipError_t e = launch_encode(c->d.wavelet, c->nplanes, c->n_tiles, c->d.tile, c->d.levels, qstep, src,
+                               coeffs, c->enc_ws, c->enc_flag, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  hipFree(ws);
-  if (flag) hipFree(flag);
   if (e != hipSuccess) return hip_fail(e, "wv_encode_intra");
-  if (h_flag) return fail(WV_EINVAL, "a quantisation index falls outside int16 (raise qstep)");
+  if (*(volatile int*)c->enc_flag) {
+    *c->enc_flag = 0;
+    return fail(WV_EINVAL, "a quantisation index falls outside int16 (raise qstep)");
+  }
   return WV_OK;
 }
 

@@ -42,6 +42,11 @@ struct wv_ctx {
   unsigned char* tab_dev = nullptr;
   hipEvent_t tab_done[wvp::kTableSlots] = {};
   int tab_next = 0;
+  // encoder: device workspace (allocated by the first call that needs one,
+  // kept until the context is destroyed) and overflow flag (pinned, the tail
+  // of tab_host; 0 between calls)
+  void* enc_ws = nullptr;
+  int* enc_flag = nullptr;
 };
 
 namespace wvp {

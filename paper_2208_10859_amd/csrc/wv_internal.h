@@ -126,8 +126,12 @@ struct RebuildArgs {
 };
 static_assert(sizeof(RebuildArgs) <= 4000, "kernel arguments must stay under 4 KB");
 hipError_t launch_rebuild(int wavelet, const RebuildArgs& a, hipStream_t s);
+// Intra encoder (wv_encode.hip): device workspace it needs (0: none), and its
+// launches; *overflow (host-visible) is set to 1 when a 5/3 index falls
+// outside int16.
+size_t encode_workspace_bytes(int wavelet, int nplanes, int n_tiles, int tile, int levels);
 hipError_t launch_encode(int wavelet, int nplanes, int n_tiles, int tile, int levels,
                          int qstep, const void* const* src, void* const* dst, void* ws,
-                         int* overflow_flag, hipStream_t s);
+                         int* overflow, hipStream_t s);
 
 }  // namespace wv

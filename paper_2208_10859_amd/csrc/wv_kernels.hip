@@ -1,6 +1,5 @@
 // HIP kernels for gfx950: the plain per-step decode (one launch per step
-// and level through an HBM workspace) and the intra encoder used to build
-// coefficient stores.
+// and level through an HBM workspace).
 #include "wv_dev.h"
 #include "wv_internal.h"
 
@@ -180,119 +179,6 @@ hipError_t launch_plain(int wavelet, int format, const PlainArgs& a, hipStream_t
                                : launch_plain_t<Inv53, WV_GRAY8>(a, s);
   return format == WV_YUV420 ? launch_plain_t<Inv97, WV_YUV420>(a, s)
                              : launch_plain_t<Inv97, WV_GRAY8>(a, s);
-}
-
-// ================================================================= encoder
-template <class V>
-__global__ __launch_bounds__(256) void k_enc_load(const uint8_t* __restrict__ src,
-                                                  V* __restrict__ ws, size_t n) {
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e < n) ws[e] = (V)src[e];
-}
-
-// One forward level, one direction, in place: each group owns lines of one
-// tile (rows: 4 rows; columns: 16 adjacent columns).
-template <class LF, bool ROWS>
-__global__ __launch_bounds__(256) void k_enc_level(typename LF::V* __restrict__ ws, int P,
-                                                   int l) {
-  using V = typename LF::V;
-  constexpr int RPW = 4, CPW = sizeof(V) == 8 ? 8 : 16;
-  __shared__ V line[ROWS ? RPW * kMaxTile : kMaxTile * CPW];
-  const int n = P >> (l - 1), h = n >> 1;
-  V* t = ws + (size_t)blockIdx.y * P * P;
-  const int nl = ROWS ? RPW : CPW;
-  const int l0 = blockIdx.x * nl;
-  if (l0 >= n) return;
-  const int cnt = min(nl, n - l0);
-  const int tid = threadIdx.x;
-  for (int i = tid; i < cnt * n; i += 256) {
-    if (ROWS) {
-      const int r = i / n, c = i - r * n;
-      line[r * n + c] = t[(size_t)(l0 + r) * P + c];
-    } else {
-      const int r = i / cnt, c = i - r * cnt;
-      line[r * CPW + c] = t[(size_t)r * P + l0 + c];
-    }
-  }
-  __syncthreads();
-  for (int i = tid; i < cnt * h; i += 256) {
-    int ln, k;
-    if (ROWS) { ln = i / h; k = i - ln * h; }
-    else { k = i / cnt; ln = i - k * cnt; }
-    auto x = [&](int j) -> V {
-      const int q = wss(j, n);
-      return ROWS ? line[ln * n + q] : line[q * CPW + ln];
-    };
-    V s, d;
-    LF::pair(x, k, s, d);
-    if (ROWS) {
-      t[(size_t)(l0 + ln) * P + k] = s;
-      t[(size_t)(l0 + ln) * P + h + k] = d;
-    } else {
-      t[(size_t)k * P + l0 + ln] = s;
-      t[(size_t)(h + k) * P + l0 + ln] = d;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void k_enc_quant53(const int* __restrict__ ws,
-                                                     int16_t* __restrict__ dst, size_t n,
-                                                     int step, int* overflow) {
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= n) return;
-  const int c = ws[e];
-  const int a = (2 * abs(c) + step) / (2 * step);
-  const int q = c < 0 ? -a : a;
-  if (q < -32768 || q > 32767) atomicOr(overflow, 1);
-  dst[e] = (int16_t)q;
-}
-
-__global__ __launch_bounds__(256) void k_enc_quant97(const double* __restrict__ ws,
-                                                     float* __restrict__ dst, size_t n,
-                                                     int step) {
-  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= n) return;
-  const double c = ws[e];
-  const double a = floor(fabs(c) / step + 0.5);
-  dst[e] = (float)(step * (c < 0 ? -a : a));
-}
-
-template <class LF>
-static hipError_t launch_encode_t(int nplanes, int n_tiles, int tile, int levels, int qstep,
-                                  const void* const* src, void* const* dst, void* ws,
-                                  int* overflow, hipStream_t s) {
-  using V = typename LF::V;
-  for (int p = 0; p < nplanes; ++p) {
-    const int P = p == 0 ? tile : tile / 2;
-    const size_t n = (size_t)n_tiles * P * P;
-    const unsigned g = (unsigned)((n + 255) / 256);
-    hipLaunchKernelGGL(k_enc_load<V>, dim3(g), dim3(256), 0, s, (const uint8_t*)src[p], (V*)ws,
-                       n);
-    for (int l = 1; l <= levels; ++l) {
-      const int m = P >> (l - 1);
-      const int cpw = sizeof(V) == 8 ? 8 : 16;
-      hipLaunchKernelGGL((k_enc_level<LF, false>), dim3((m + cpw - 1) / cpw, n_tiles), dim3(256), 0, s,
-                         (V*)ws, P, l);
-      hipLaunchKernelGGL((k_enc_level<LF, true>), dim3((m + 3) / 4, n_tiles), dim3(256), 0, s,
-                         (V*)ws, P, l);
-    }
-    if (sizeof(V) == 4)
-      hipLaunchKernelGGL(k_enc_quant53, dim3(g), dim3(256), 0, s, (const int*)ws,
-                         (int16_t*)dst[p], n, qstep, overflow);
-    else
-      hipLaunchKernelGGL(k_enc_quant97, dim3(g), dim3(256), 0, s, (const double*)ws,
-                         (float*)dst[p], n, qstep);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_encode(int wavelet, int nplanes, int n_tiles, int tile, int levels, int qstep,
-                         const void* const* src, void* const* dst, void* ws, int* overflow,
-                         hipStream_t s) {
-  if (wavelet == WV_W53)
-    return launch_encode_t<Fwd53>(nplanes, n_tiles, tile, levels, qstep, src, dst, ws, overflow,
-                                  s);
-  return launch_encode_t<Fwd97>(nplanes, n_tiles, tile, levels, qstep, src, dst, ws, overflow, s);
 }
 
 }  // namespace wv

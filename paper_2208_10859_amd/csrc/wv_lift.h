@@ -1,5 +1,6 @@
 // Device-side lifting building blocks shared by the fused, plain and encoder
-// kernels: symmetric extension and one output pair of each 1D transform.
+// kernels: symmetric extension, the lifting constants, and one output pair of
+// each inverse 1D transform.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -102,46 +103,6 @@ struct Inv97 {
       x[2 * t] = e2[t];
       x[2 * t + 1] = o1[t + 1] - A * (e2[t] + e2[t + 1]);
     }
-  }
-};
-
-// --------------------------------------------------------------- forward 5/3
-// Low/high output k of a line read through x(i) (any index; the accessor
-// applies the symmetric extension).
-struct Fwd53 {
-  using V = int;
-  template <class X>
-  __device__ static __forceinline__ void pair(X x, int k, V& s, V& d) {
-    const int xm2 = x(2 * k - 2), xm1 = x(2 * k - 1), x0 = x(2 * k), x1 = x(2 * k + 1),
-              x2 = x(2 * k + 2);
-    const int dk = x1 - ((x0 + x2) >> 1);
-    const int dkm1 = xm1 - ((xm2 + x0) >> 1);
-    d = dk;
-    s = x0 + ((dkm1 + dk + 2) >> 2);
-  }
-};
-
-// --------------------------------------------------------------- forward 9/7
-struct Fwd97 {
-  using V = double;
-  template <class X>
-  __device__ static __forceinline__ void pair(X x, int k, V& s, V& d) {
-    const double A = WV_A97, B = WV_B97, G = WV_G97, D = WV_D97, K = WV_K97;
-    const double em2 = x(2 * k - 4), em1 = x(2 * k - 2), e0 = x(2 * k), e1 = x(2 * k + 2),
-                 e2 = x(2 * k + 4);
-    const double om2 = x(2 * k - 3), om1 = x(2 * k - 1), o0 = x(2 * k + 1), o1 = x(2 * k + 3);
-    const double p_m2 = om2 + A * (em2 + em1);
-    const double p_m1 = om1 + A * (em1 + e0);
-    const double p_0 = o0 + A * (e0 + e1);
-    const double p_1 = o1 + A * (e1 + e2);
-    const double f_m1 = em1 + B * (p_m2 + p_m1);
-    const double f_0 = e0 + B * (p_m1 + p_0);
-    const double f_1 = e1 + B * (p_0 + p_1);
-    const double q_m1 = p_m1 + G * (f_m1 + f_0);
-    const double q_0 = p_0 + G * (f_0 + f_1);
-    const double g_0 = f_0 + D * (q_m1 + q_0);
-    s = g_0 / K;
-    d = q_0 * K;
   }
 };
 
