@@ -34,6 +34,7 @@ bool variant_fits(const wv_desc& d, const Variant* v) {
   if (v && v->wavelet >= 0 && v->wavelet != d.wavelet) return false;
   if (v && v->kind == 2)   // row strips: compiled for one tile edge and level count
     return d.tile == v->bw && d.levels == v->levels;
+  if (v && v->kind == 3) return d.tile == v->bw;   // whole tiles: any level count
   const int min_edge = d.format == WV_YUV420 ? d.tile / 2 : d.tile;
   if (v && !v->general && (min_edge >> (d.levels - 1)) < 16) return false;
   if (v && v->levels != 0 && v->levels != d.levels) return false;
@@ -108,10 +109,7 @@ wv_status wv_create(wv_ctx** out, const wv_desc* desc) {
     wv_destroy(c);
     return st;
   }
-  // default variant: the first that fits the tile geometry
-  c->variant = -1;
-  for (int v = 0; v < fused_variant_count(desc->wavelet, desc->format); ++v)
-    if (variant_fits(c->d, fused_variant(desc->wavelet, desc->format, v))) { c->variant = v; break; }
+  c->variant = default_variant(c->d);
   if (c->variant < 0) {
     wv_destroy(c);
     return fail(WV_EUNSUPPORTED, "no fused variant fits tile %d", desc->tile);
@@ -342,9 +340,9 @@ extern "C" wv_status wv_decode_gop(wv_ctx* c, int32_t n_frames, const wv_frame* 
   if (plan.items.empty()) return WV_OK;
   const Variant* var = fused_variant(c->d.wavelet, c->d.format, c->variant);
   wv_status st = WV_OK;
-  if (c->path == WV_PATH_FUSED && var->kind == 2) {
+  if (c->path == WV_PATH_FUSED && var->kind >= 2) {
     // one launch per group of up to kArgJobs frames: each unit takes its tile
-    // strip through the group's frames in order
+    // (strip) through the group's frames in order
     WorkArgs a;
     memset(&a, 0, sizeof a);
     fill_geometry(c, var, a);
@@ -405,12 +403,12 @@ extern "C" wv_status wv_decode_set(wv_ctx* c, const wv_set* set, int32_t t0, int
         return fail(WV_EINVAL, "wv_decode_set: qstep[%d] = %d outside 1..65535", b, set->qstep[b]);
   // the context's variant if it is a row strip, else the first row strip that fits
   const Variant* var = fused_variant(c->d.wavelet, c->d.format, c->variant);
-  if (!var || var->kind != 2) {
+  if (!var || var->kind != 2 || var->bw != 512) {
     var = nullptr;
     const int nv = fused_variant_count(c->d.wavelet, c->d.format);
     for (int v = 0; v < nv && !var; ++v) {
       const Variant* cand = fused_variant(c->d.wavelet, c->d.format, v);
-      if (cand && cand->kind == 2 && variant_fits(c->d, cand)) var = cand;
+      if (cand && cand->kind == 2 && cand->bw == 512 && variant_fits(c->d, cand)) var = cand;
     }
     if (!var)
       return fail(WV_EUNSUPPORTED, "wv_decode_set: no row-strip kernel for tile %d with %d levels",

@@ -44,6 +44,25 @@ __device__ __forceinline__ void to_rgb(float y, float cb, float cr, float& r, fl
   b = clip255(y + 1.772f * cb);
 }
 
+// Byte permutation (V_PERM_B32): byte i of the result is byte sel_i of the
+// eight bytes {lo (0..3), hi (4..7)}; selector 0x0c gives 0x00, 0x0d 0xff.
+__device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
+  return __builtin_amdgcn_perm(hi, lo, sel);
+}
+// Byte packing of values already clipped to 0..255, as byte permutations.
+// Packing with shifts and ORs let instruction selection fold a preceding
+// shift and clamp of two values into V_ASHR_PK_U8_I32, which writes only the
+// low half of its destination, while the code this toolchain generated after
+// it ORed further bytes into the upper half as if it were zero: the
+// register's stale bytes reached the output (clipped odd rows of the 5/3
+// inverse, (a + b) >> 1 with no residual).  A permutation of whole registers
+// offers no such pattern.
+__device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
+  const uint32_t ab = perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);   // a0 b0 0 0
+  const uint32_t cd = perm((uint32_t)d, (uint32_t)c, 0x0c0c0400u);   // c0 d0 0 0
+  return perm(cd, ab, 0x05040100u);                                   // a0 b0 c0 d0
+}
+
 // Level windows of a block, one dimension.  Level 1's computed window C_1
 // is the block itself.  Level k needs the low-band samples
 // [C_k.a/2 - S_LO, C_k.b/2 + S_HI) of level k+1's output; that range rounded

@@ -18,6 +18,7 @@
 //
 // No intermediate level touches HBM.  The only traffic is the coefficient
 // windows, the reference block and the output block.
+#include "wv_ctx.h"
 #include "wv_fused_common.h"
 
 namespace wv {
@@ -359,8 +360,19 @@ __global__ __launch_bounds__((BW / 2) * (BH / TR)) void k_fused(const WorkArgs a
   X("strip_r32_w4_L3_chain_grid", 32, 4, false, 0, 3, 3) \
   X("strip_r16_w4_L3_chain_grid", 16, 4, false, 0, 3, 4)
 
-// Strip variants come first, then the fast block variants: the default
-// variant of a context is the first one that fits its geometry.
+// Row strips of narrower tiles (16 rows, 4 waves, chain schedule): name, tile,
+// level count.
+#define WV_NARROW_VARIANTS(X) \
+  X("strip256_r16_w4_L2_chain_grid", 256, 2) \
+  X("strip256_r16_w4_L3_chain_grid", 256, 3) \
+  X("strip256_r16_w4_L4_chain_grid", 256, 4) \
+  X("strip256_r16_w4_L5_chain_grid", 256, 5) \
+  X("strip128_r16_w4_L2_chain_grid", 128, 2) \
+  X("strip128_r16_w4_L3_chain_grid", 128, 3) \
+  X("strip128_r16_w4_L4_chain_grid", 128, 4) \
+  X("strip128_r16_w4_L5_chain_grid", 128, 5)
+
+// The order is the variants' public numbering.
 static const Variant kVariants[] = {
 #define WV_S(name, r, nw, pers, gpc, lv, shape) \
   {name, 512, r, 64 * nw, pers, gpc, false, lv, shape, 2, -1, -1},
@@ -374,6 +386,12 @@ static const Variant kVariants[] = {
   {name, bw, bh, (bw / 2) * (bh / tr), pers, gpc, gen, 0, -1, 0, -1, -1},
     WV_VARIANTS(WV_V)
 #undef WV_V
+#define WV_N(name, tile, lv) {name, tile, 16, 256, false, 0, false, lv, 4, 2, -1, -1},
+    WV_NARROW_VARIANTS(WV_N)
+#undef WV_N
+    {"tile64_grid", 64, 64, 512, false, 0, true, 0, 0, 3, -1, -1},
+    {"tile32_grid", 32, 32, 256, false, 0, true, 0, 0, 3, -1, -1},
+    {"tile16_grid", 16, 16, 128, false, 0, true, 0, 0, 3, -1, -1},
 };
 #define WV_ONE(...) +1
 static constexpr int kNumSpecial = 0 WV_STRIP_VARIANTS(WV_ONE) WV_FAST_VARIANTS(WV_ONE);
@@ -383,6 +401,26 @@ static constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 int fused_variant_count(int, int) { return kNumVariants; }
 const Variant* fused_variant(int, int, int v) {
   return (v >= 0 && v < kNumVariants) ? &kVariants[v] : nullptr;
+}
+
+// The variant a new context starts with: whole tiles and narrow strips where
+// they fit (tiles up to 256), else the first that fits.  GPU time of a YUV420
+// frame of 120 tiles (us, first block variant -> this choice), 5/3 and 9/7:
+//   tile 16, 3 levels:  23.2 -> 6.0,  40.1 -> 7.4
+//   tile 32, 4 levels:  31.9 -> 7.2,  52.2 -> 9.2
+//   tile 64, 4 levels:  30.9 -> 8.6,  48.3 -> 11.2
+//   tile 128, 3 levels: 24.5 -> 9.5,  36.8 -> 14.9
+//   tile 256, 5 levels: 92.7 -> 24.5, 181.1 -> 43.5
+// and of one tile (tile 16 .. 256, 5/3): 21.0 -> 5.7, 30.6 -> 6.9, 30.2 -> 8.0,
+// 19.8 -> 5.9, 38.2 -> 8.0.
+int default_variant(const wv_desc& d) {
+  for (int v = 0; v < kNumVariants; ++v) {
+    const Variant& var = kVariants[v];
+    if ((var.kind == 3 || (var.kind == 2 && var.bw < 512)) && wvp::variant_fits(d, &var)) return v;
+  }
+  for (int v = 0; v < kNumVariants; ++v)
+    if (wvp::variant_fits(d, &kVariants[v])) return v;
+  return -1;
 }
 
 template <class LF, int FMT>
@@ -400,7 +438,12 @@ static hipError_t launch_fused_t(int v, const WorkArgs& a, int n_cu, hipStream_t
   WV_VARIANTS(WV_L)
 #undef WV_L
   const Variant* var = fused_variant(0, FMT, v);
+  constexpr bool W53 = std::is_same<LF, Inv53>::value;
+  if (var && var->kind == 3) return launch_tile(W53 ? WV_W53 : WV_W97, FMT, var->bw, a, s);
   if (!var || var->levels == 0) return hipErrorInvalidValue;
+  if (var->kind == 2 && var->bw < 512)
+    return W53 ? launch_strip53_small(FMT, var->bw, var->levels, a, s)
+               : launch_strip97_small(FMT, var->bw, var->levels, a, s);
   if (var->kind == 2)
     return std::is_same<LF, Inv53>::value
                ? launch_strip53(FMT, var->shape, var->levels, var->persistent, a, n_cu, s)

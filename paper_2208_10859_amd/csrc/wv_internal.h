@@ -84,7 +84,7 @@ struct Variant {
   bool general;          // handles mirrored regions smaller than 16 samples
   int levels;            // fast and strip variants: the level count they are compiled for (0 = any)
   int shape;             // fast and strip variants: shape index in their launcher
-  int kind;              // 0 block (runtime level count), 1 fast block, 2 row strip
+  int kind;              // 0 block (runtime level count), 1 fast block, 2 row strip, 3 whole tile
   int format;            // the only format it is built for, or -1 for both
   int wavelet;           // the only wavelet it is built for, or -1 for both
 };
@@ -92,6 +92,7 @@ struct Variant {
 // Launchers (wv_kernels.hip).  Return hipSuccess or the launch error.
 int fused_variant_count(int wavelet, int format);
 const Variant* fused_variant(int wavelet, int format, int v);
+int default_variant(const wv_desc& d);   // -1: none fits
 hipError_t launch_fused(int wavelet, int format, int v, const WorkArgs& a, int n_cu,
                         hipStream_t s);
 hipError_t launch_fast53(int format, int shape, int L, bool pers, const WorkArgs& a, int n_cu,
@@ -102,6 +103,9 @@ hipError_t launch_strip53(int format, int shape, int L, bool pers, const WorkArg
                           hipStream_t s);
 hipError_t launch_strip97(int format, int shape, int L, bool pers, const WorkArgs& a, int n_cu,
                           hipStream_t s);
+hipError_t launch_strip53_small(int format, int tile, int L, const WorkArgs& a, hipStream_t s);
+hipError_t launch_strip97_small(int format, int tile, int L, const WorkArgs& a, hipStream_t s);
+hipError_t launch_tile(int wavelet, int format, int tile, const WorkArgs& a, hipStream_t s);
 // Inter-frame-set frames (jobs with the hstride / hband / hq fields), grid form.
 hipError_t launch_strip53_set(int format, int shape, int L, const WorkArgs& a, hipStream_t s);
 hipError_t launch_strip97_set(int format, int shape, int L, const WorkArgs& a, hipStream_t s);

@@ -361,24 +361,6 @@ struct RefRows<float, C> {
   __device__ __forceinline__ float get(int row, int c) const { return v[row][c]; }
 };
 
-// Byte permutation (V_PERM_B32): byte i of the result is byte sel_i of the
-// eight bytes {lo (0..3), hi (4..7)}; selector 0x0c gives 0x00, 0x0d 0xff.
-__device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
-  return __builtin_amdgcn_perm(hi, lo, sel);
-}
-// Byte packing of values already clipped to 0..255, as byte permutations.
-// Packing with shifts and ORs let instruction selection fold a preceding
-// shift and clamp of two values into V_ASHR_PK_U8_I32, which writes only the
-// low half of its destination, while the code this toolchain generated after
-// it ORed further bytes into the upper half as if it were zero: the
-// register's stale bytes reached the output (clipped odd rows of the 5/3
-// inverse, (a + b) >> 1 with no residual).  A permutation of whole registers
-// offers no such pattern.
-__device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
-  const uint32_t ab = perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);   // a0 b0 0 0
-  const uint32_t cd = perm((uint32_t)d, (uint32_t)c, 0x0c0c0400u);   // c0 d0 0 0
-  return perm(cd, ab, 0x05040100u);                                   // a0 b0 c0 d0
-}
 __device__ __forceinline__ uint16_t pack2(int a, int b) {
   return (uint16_t)perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);
 }
@@ -509,13 +491,12 @@ struct Smem {
   static constexpr bool ALIAS = NC && SCHED == 1;
   static constexpr int YB = win_elems<LF>(R, P, L, 1);
   static constexpr int CA = NC ? win_elems<LF>(R / 2, P / 2, L, 0) : 1;
-  static constexpr int CB = NC ? win_elems<LF>(R / 2, P / 2, L, 1) : 1;
+  static constexpr int CB = NC ? (win_elems<LF>(R / 2, P / 2, L, 1) + 3) & ~3 : 1;   // 16-byte multiples
   static constexpr int Y4 = (win_elems_from4<LF>(R, P, L) + 3) & ~3;   // keeps cb 16-byte aligned
   static constexpr int YA0 = win_elems<LF>(R, P, L, 0);
   static constexpr int YA = ALIAS ? (YA0 > Y4 + NC * CB ? YA0 : Y4 + NC * CB) : YA0;
   static constexpr int CBS = ALIAS ? 1 : CB;                            // separate cb storage
   static constexpr int CHR = NC ? (R / 2) * (P / 2) : 4;
-  static_assert(!ALIAS || CB % 4 == 0, "chroma windows keep 16-byte alignment");
   alignas(16) V ya_[YA];
   alignas(16) V yb[YB];
   alignas(16) V ca[NC ? NC : 1][CA];
@@ -1043,6 +1024,16 @@ constexpr int seg_pairs() {
   }
 }
 
+// Pairs per segment of the finest chroma rows (strips of ROWS rows): 4, or
+// fewer where several rows sit side by side in a wave, so that every row slot
+// holds a whole segment of the strip.
+template <int N, int ROWS>
+constexpr int chroma_pairs() {
+  constexpr int k = ROWS / 2 / RL<N>::S;
+  static_assert(k >= 1, "chroma rows fill the wave's row slots");
+  return k < 4 ? k : 4;
+}
+
 // Level l of one plane: the pairs of its cone rows [a, b) in segments of K,
 // dealt to `nwp` waves (this wave is number `rank` among them; with several
 // rows per wave each lane slot takes its own segment).
@@ -1193,7 +1184,7 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
   // inter-frame-set frames stand alone: no reference is read or written
   const bool intra = SET || (job.flags & kJobIntra) != 0;
   const bool has_out = (job.flags & kJobHasOut) != 0;
-  constexpr bool KEEPY = sizeof(RT) == 1 && YUV && !SET, KEEPC = YUV && !SET;
+  constexpr bool KEEPY = sizeof(RT) == 1 && YUV && !SET && RL<P>::C % 4 == 0, KEEPC = YUV && !SET;
   const bool wref_y = !KEEPY || last, wref_c = !KEEPC || last;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   int lane = threadIdx.x & 63;
@@ -1270,7 +1261,7 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
     // the finest rows of chroma plane pi
     auto chroma1 = [&](auto PI, int rank, int nwp) __attribute__((always_inline)) {
       constexpr int pi = decltype(PI)::value;
-      constexpr int KC = 4, C = RL<PC>::C;
+      constexpr int KC = chroma_pairs<PC, RC>(), C = RL<PC>::C;
       const Plane<LF, L, SrcT>& pl = pc[pi];
       RT* chr = sm.chr[pi];
       level<LF, PC, L, 1, KC>(pl, qs, lc, rank, nwp, lane, [&](int g, int j0, int) {
@@ -1396,7 +1387,7 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
             if constexpr (lcv >= 2) {
               coarse_level<LF, PC, L, lcv, seg_pairs<LF, (PC >> (lcv - 1)), RC, lcv, (do_y ? (NW + 2) / 3 : (NW + 1) / 2)>()>(pl, qs, lc, rank, nwp, lane);
             } else {
-              constexpr int KC = 4, C = RL<PC>::C;
+              constexpr int KC = chroma_pairs<PC, RC>(), C = RL<PC>::C;
               RT* chr = sm.chr[pi];
               level<LF, PC, L, 1, KC>(pl, qs, lc, rank, nwp, lane, [&](int g, int j0, int) {
                 ChromaOut<LF, PC, C, !SET> e;
