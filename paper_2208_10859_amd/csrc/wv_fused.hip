@@ -413,10 +413,19 @@ const Variant* fused_variant(int, int, int v) {
 //   tile 256, 5 levels: 92.7 -> 24.5, 181.1 -> 43.5
 // and of one tile (tile 16 .. 256, 5/3): 21.0 -> 5.7, 30.6 -> 6.9, 30.2 -> 8.0,
 // 19.8 -> 5.9, 38.2 -> 8.0.
+// 512-sample YUV420 tiles: the 16-row chain strips, whose five (9/7: three)
+// resident units per CU hide each other's latency, against the 32-row phased
+// ones that come first (us, five levels, 1 and 36 tiles): a 5/3 frame 13.7 -> 9.0
+// and 23.0 -> 21.6, its GOP of 8 88.3 -> 52.4 and 160.9 -> 148.3; a 9/7 frame
+// 22.0 -> 15.2 and 80.3 -> 53.9, its GOP 159.8 -> 104.6 and 684.4 -> 492.4.  Grey
+// frames have no chroma chains to run beside the luma one, and the 32-row form
+// stays the better one there (36 tiles: a 5/3 frame 14.5 against 15.5, a 9/7
+// frame 34.0 against 35.6).
 int default_variant(const wv_desc& d) {
   for (int v = 0; v < kNumVariants; ++v) {
     const Variant& var = kVariants[v];
-    if ((var.kind == 3 || (var.kind == 2 && var.bw < 512)) && wvp::variant_fits(d, &var)) return v;
+    const bool chain512 = var.bw == 512 && var.shape == 4 && !var.persistent && d.format == WV_YUV420;
+    if ((var.kind == 3 || (var.kind == 2 && (var.bw < 512 || chain512))) && wvp::variant_fits(d, &var)) return v;
   }
   for (int v = 0; v < kNumVariants; ++v)
     if (wvp::variant_fits(d, &kVariants[v])) return v;
