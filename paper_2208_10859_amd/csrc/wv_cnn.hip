@@ -407,153 +407,189 @@ __global__ __launch_bounds__(256) void k_wsum(const float* __restrict__ part, in
 }
 
 // The whole forward pass in one kernel (3 -> 32 -> 32 -> 32 -> 3): a
-// workgroup computes a 16 x 32 output tile and keeps every intermediate
+// workgroup computes a 14 x 26 output tile and keeps every intermediate
 // activation on chip.  Each layer is computed on the region the next one
-// needs -- the tile grown by one pixel per remaining layer (22 x 38, 20 x 36,
-// 18 x 34 pixels) -- so that no activation is read back from memory; pixels
+// needs -- the tile grown by one pixel per remaining layer (20 x 32, 18 x 30,
+// 16 x 28 pixels) -- so that no activation is read back from memory; pixels
 // of a region outside the image are zero, the padding every layer applies.
-// The four weight matrices (50 KB of bf16) and the image patch are staged in
-// LDS once; each layer's matrix is then copied into registers by every wave.
-// The MFMA operand layout and K order are k_conv's (above); activations are
-// rounded to bfloat16 after the ReLU, as the backward pass reads them.  KEEP:
-// also write the three ReLU activations of the tile's own pixels to memory
-// for the backward pass.  Sixteen waves (four per SIMD) hide the LDS and
-// barrier latencies of the one workgroup that fits a CU.
-constexpr int FH = 16, FW = 32;                       // output tile
-constexpr int FWAVES = 16;                            // waves per workgroup (four per SIMD)
-constexpr int kW1 = 32 * 64, kW2 = 32 * 288, kW4 = 16 * 288;
-constexpr int kWAll = kW1 + 2 * kW2 + kW4;            // bf16 weights of the four layers
+// Activations are rounded to bfloat16 after the ReLU, as the backward pass
+// reads them.  KEEP: also write the three ReLU activations of the tile's own
+// pixels to memory for the backward pass.
+//
+// Every region has rows of 32 pixels, two blocks of 16 columns.  A wave takes
+// one of them and half of the layer's rows and streams down the input rows:
+// an operand (16 pixels, 32 channels) is read from LDS once, a row ahead, and
+// multiplied into the three output rows that it reaches, so that a row of
+// outputs costs three LDS reads instead of nine; per output the taps still
+// come in the order (ky, kx).  The layer's weights stay in registers (18
+// operands), loaded from global memory in operand order while the slower waves
+// finish the layer before: they are the same for every workgroup, and in LDS
+// they took 50 KB and as many reads as the activations.
+// Two workgroups of four waves fit a CU (78 KB of LDS) and fill each other's
+// barriers; with six waves each, whose thirds do not divide over four SIMDs,
+// only one was resident (2048 x 2048: 414 us).
+// What bounds it: instruction issue of the matrix cores (busy 0.5 of the time
+// at the clock they run at) and of the epilogue's vector work between them.
+// 2048 x 2048, inference: 422 -> 269 us; 16 x 128 x 128 with the activations
+// kept: 33.5 -> 32.6.  Tiles of 8 / 10 / 12 rows: 305 / 302 / 280 us.
+constexpr int FH = 14, FW = 26;                       // output tile
+constexpr int FWAVES = 4;                             // waves per workgroup
+constexpr int FP = 32;                                // pixels per region row
 
 struct FwdArgs {
-  const uint16_t* w[4];    // bf16 weights, [coutp][kpad32(cin)]
+  const uint16_t* w[4];    // bf16 weights in operand order, see prep_one
   const float* b[4];       // fp32 biases
   uint16_t* act[3];        // ReLU outputs, [pixels][32] (KEEP)
 };
 
+// A layer's weights and biases as a lane holds them.
+template <int LI>
+struct FwdW {
+  static constexpr int CIN = LI == 1 ? 4 : 32, COUT = LI == 4 ? 16 : 32, NB = COUT / 16, KS = kpad32(CIN) / 32;
+  bf8 w[KS][NB];
+  float b[NB][4];
+  __device__ __forceinline__ void load(const FwdArgs& fa, int lane) {
+    const uint4* p = (const uint4*)fa.w[LI - 1] + lane;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) w[ks][nb] = as_bf8(p[(ks * NB + nb) * 64]);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int co = nb * 16 + 4 * (lane >> 4) + q;
+        b[nb][q] = (LI < 4 || co < 3) ? fa.b[LI - 1][co] : 0.f;
+      }
+  }
+};
+
 // One layer from LDS region `in` to region `out` (LI = 1..3) or to z (LI = 4).
-// Regions are row-major pixel arrays; 32-channel ones are four planes of
-// 8-channel (16-byte) pixels with a stride of PIN / POUT entries.
+// 32-channel regions are four planes of 8-channel (16-byte) pixels, a multiple
+// of 256 bytes apart (an operand read then spreads over all banks); columns
+// past a region's width hold values that no needed output reads.
 template <int LI, bool KEEP>
-__device__ __forceinline__ void fwd_layer(const void* in, uint4* out, const uint16_t* wl, const float* __restrict__ bias,
-                                          uint16_t* __restrict__ act, float* __restrict__ z, int n, int H, int W,
-                                          int y0, int x0, int wave, int lane) {
-  constexpr int CIN = LI == 1 ? 4 : 32, COUT = LI == 4 ? 16 : 32, NB = COUT / 16;
-  constexpr int KP = kpad32(CIN), KS = KP / 32;
-  constexpr int GROW = 4 - LI;                             // output region: tile grown by GROW
-  constexpr int HO = FH + 2 * GROW, WO = FW + 2 * GROW, WI = WO + 2;
-  constexpr int NPX = HO * WO, NPB = (NPX + 15) / 16;
-  constexpr int PIN = (HO + 2) * WI + 1, POUT = NPX + 1;   // plane strides (32-channel regions)
-  // every 16-pixel block of the wave in one pass: G blocks, computed without
-  // a branch (blocks past the region read clamped pixels and are dropped at
-  // the end), so that each K step's LDS reads go out together
-  constexpr int G = (NPB + FWAVES - 1) / FWAVES;
+__device__ __forceinline__ void fwd_layer(const FwdW<LI>& wt, const void* in, uint4* out, uint16_t* __restrict__ act,
+                                          float* __restrict__ z, int n, int H, int W, int y0, int x0, int wave,
+                                          int lane) {
+  constexpr int NB = FwdW<LI>::NB, GROW = 4 - LI;
+  constexpr int HO = FH + 2 * GROW, WO = FW + 2 * GROW, RPG = (HO + FWAVES / 2 - 1) / (FWAVES / 2);
+  constexpr int PIN = (HO + 2) * FP, POUT = HO * FP;       // plane strides (32-channel regions)
   const int i16 = lane & 15, g = lane >> 4;
-  const int oy0 = y0 - GROW, ox0 = x0 - GROW;               // image position of the region's origin
+  const int rs = min((wave >> 1) * RPG, HO - RPG), col = (wave & 1) * 16 + i16;
+  const int gx = x0 - GROW + col;
+  const bool colin = gx >= 0 && gx < W;
+  const bool own = col >= GROW && col < GROW + FW;
+  // the region reaches over the image's edge (uniform)
+  const bool border = y0 < GROW || x0 < GROW || y0 + FH + GROW > H || x0 + FP - GROW > W;
+  uint2* obase = (uint2*)out + ((g >> 1) * POUT + rs * FP + col) * 2 + (g & 1);
 
-  bf8 wr[KS][NB];
+  auto finish = [&](int r, const f4 (&acc)[NB]) __attribute__((always_inline)) {
+    const int oy = rs + r, gy = y0 - GROW + oy;
+    const bool rowin = gy >= 0 && gy < H;
+    if constexpr (LI == 4) {
+      if (g == 0 && rowin && colin && col < WO)
+        *(float4*)(z + ((size_t)(n * H + gy) * W + gx) * 4) =
+            make_float4(acc[0][0] + wt.b[0][0], acc[0][1] + wt.b[0][1], acc[0][2] + wt.b[0][2], 0.f);
+    } else {
+      const bool inside = rowin && colin;
+      const bool keep = KEEP && inside && own && oy >= GROW && oy < GROW + FH;
+      uint2* o = obase + r * FP * 2;
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
+      for (int nb = 0; nb < NB; ++nb) {
+        float v[4];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) wr[ks][nb] = as_bf8(*(const uint4*)(wl + (nb * 16 + i16) * KP + ks * 32 + 8 * g));
-  float bv[NB][4];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int co = nb * 16 + 4 * g + q;
-      bv[nb][q] = (LI < 4 || co < 3) ? bias[co] : 0.f;
+        for (int q = 0; q < 4; ++q) v[q] = fmaxf(acc[nb][q] + wt.b[nb][q], 0.f);
+        uint2 p = make_uint2(pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3]));
+        if (border && !inside) p = make_uint2(0u, 0u);
+        o[2 * nb * POUT * 2] = p;
+        if (keep) *(uint2*)(act + ((size_t)(n * H + gy) * W + gx) * 32 + nb * 16 + 4 * g) = p;
+      }
     }
+  };
 
-  for (int pb0 = wave; pb0 < NPB; pb0 += FWAVES * G) {
-    f4 acc[G][NB];
-    int pix[G], src[G];
+  if constexpr (LI == 1) {
+    // K step 0: taps 2 g and 2 g + 1 of four channels each; step 1: tap 8
+    constexpr int WI = FP + 2;
+    const uint2* p0 = (const uint2*)in + rs * WI + col;
+    const int ta = 2 * g, tb = 2 * g + 1;
+    const uint2* pa = p0 + (ta / 3) * WI + ta % 3;
+    const uint2* pb = p0 + (tb / 3) * WI + tb % 3;
+    const uint2* pc = p0 + 2 * WI + 2;
+    auto read = [&](int r, uint2 (&v)[3]) __attribute__((always_inline)) {
+      v[0] = pa[r * WI];
+      v[1] = pb[r * WI];
+      v[2] = pc[r * WI];
+    };
+    f4 acc[2][NB];     // output row r in slot r % 2
+    uint2 v[2][3];
+    read(0, v[0]);
 #pragma unroll
-    for (int gi = 0; gi < G; ++gi) {
-      pix[gi] = (pb0 + FWAVES * gi) * 16 + i16;
-      const int pc = min(pix[gi], NPX - 1), oy = pc / WO, ox = pc - oy * WO;
-      src[gi] = oy * WI + ox;                                 // input pixel of tap (0, 0)
+    for (int r = 0; r < RPG; ++r) {
+      if (r + 1 < RPG) read(r + 1, v[(r + 1) & 1]);
+      const uint2 a = v[r & 1][0], b = v[r & 1][1], c = g ? make_uint2(0u, 0u) : v[r & 1][2];
+      const bf8 b0 = as_bf8(make_uint4(a.x, a.y, b.x, b.y)), b1 = as_bf8(make_uint4(c.x, c.y, 0u, 0u));
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) acc[gi][nb] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int nb = 0; nb < NB; ++nb)
+        acc[r & 1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt.w[0][nb], b0, f4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        acc[r & 1][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt.w[1][nb], b1, acc[r & 1][nb], 0, 0, 0);
+      if (r > 0) finish(r - 1, acc[(r - 1) & 1]);
     }
+    finish(RPG - 1, acc[(RPG - 1) & 1]);
+  } else {
+    const uint4* p = (const uint4*)in + g * PIN + rs * FP + col;
+    f4 acc[4][NB];     // output row r in slot r % 4
+    uint4 b[2][3];
+    auto read = [&](int i, uint4 (&v)[3]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      uint4 bqs[G];
+      for (int kx = 0; kx < 3; ++kx) v[kx] = p[i * FP + kx];
+    };
+    read(0, b[0]);
 #pragma unroll
-      for (int gi = 0; gi < G; ++gi) {
-        uint4 bq;
-        if constexpr (CIN == 32) {
-          const int ky = ks / 3, kx = ks - 3 * (ks / 3);
-          bq = ((const uint4*)in)[g * PIN + src[gi] + ky * WI + kx];
-        } else {
-          const uint2* p8 = (const uint2*)in;
-          const int t0 = ks * 8 + 2 * g, t1 = t0 + 1;
-          const int u0 = min(t0, 8), u1 = min(t1, 8);
-          uint2 lo = p8[src[gi] + (u0 / 3) * WI + u0 % 3];
-          uint2 hi = p8[src[gi] + (u1 / 3) * WI + u1 % 3];
-          if (t0 >= 9) lo = make_uint2(0u, 0u);
-          if (t1 >= 9) hi = make_uint2(0u, 0u);
-          bq = make_uint4(lo.x, lo.y, hi.x, hi.y);
+    for (int i = 0; i < RPG + 2; ++i) {
+      if (i + 1 < RPG + 2) read(i + 1, b[(i + 1) & 1]);
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) {
+          const int r = i - ky;
+          if (r < 0 || r >= RPG) continue;
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            acc[r & 3][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                wt.w[ky * 3 + kx][nb], as_bf8(b[i & 1][kx]), ky + kx ? acc[r & 3][nb] : f4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         }
-        bqs[gi] = bq;
-      }
-#pragma unroll
-      for (int gi = 0; gi < G; ++gi) {
-        const bf8 b = as_bf8(bqs[gi]);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          acc[gi][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[ks][nb], b, acc[gi][nb], 0, 0, 0);
-      }
+      if (i >= 3) finish(i - 3, acc[(i - 3) & 3]);
     }
-    // epilogue: lane (g, i16) holds channels nb * 16 + 4 g .. + 3 of pixel pix
-#pragma unroll
-    for (int gi = 0; gi < G; ++gi) {
-      if (pb0 + FWAVES * gi >= NPB) break;
-      const int p = pix[gi];
-      if (p >= NPX) continue;
-      const int oy = p / WO, ox = p - oy * WO, gy = oy0 + oy, gx = ox0 + ox;
-      const bool inside = gy >= 0 && gy < H && gx >= 0 && gx < W;
-      if constexpr (LI == 4) {
-        if (g == 0 && inside)
-          *(float4*)(z + ((size_t)(n * H + gy) * W + gx) * 4) =
-              make_float4(acc[gi][0][0] + bv[0][0], acc[gi][0][1] + bv[0][1], acc[gi][0][2] + bv[0][2], 0.f);
-      } else {
-        const bool keep = KEEP && inside && oy >= GROW && oy < GROW + FH && ox >= GROW && ox < GROW + FW;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          float r[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) r[q] = inside ? fmaxf(acc[gi][nb][q] + bv[nb][q], 0.f) : 0.f;
-          const uint2 v = make_uint2(pk_bf16(r[0], r[1]), pk_bf16(r[2], r[3]));
-          ((uint2*)out)[((2 * nb + (g >> 1)) * POUT + p) * 2 + (g & 1)] = v;
-          if (keep) *(uint2*)(act + ((size_t)(n * H + gy) * W + gx) * 32 + nb * 16 + 4 * g) = v;
-        }
-      }
-    }
+    finish(RPG - 1, acc[(RPG - 1) & 3]);
   }
 }
 
+// Barrier for LDS hand-over: waits for no global access (the next layer's
+// weights, the activations kept).
+__device__ __forceinline__ void lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 template <bool KEEP>
-__global__ __launch_bounds__(64 * FWAVES) void k_forward(const uint16_t* __restrict__ x, const FwdArgs fa,
-                                                 float* __restrict__ z, int N, int H, int W) {
-  constexpr int R0W = FW + 8, R0H = FH + 8;
-  constexpr int PA = (FH + 6) * (FW + 6) + 1, PB = (FH + 4) * (FW + 4) + 1;
-  __shared__ __align__(16) uint16_t wl[kWAll];
-  __shared__ __align__(16) uint2 r0[R0H * R0W];
-  __shared__ __align__(16) uint4 ra[4 * PA];     // layer 1's output, then layer 3's
-  __shared__ __align__(16) uint4 rb[4 * PB];     // layer 2's output
+__global__ __launch_bounds__(64 * FWAVES) __attribute__((amdgpu_waves_per_eu(2)))
+void k_forward(const uint16_t* __restrict__ x, const FwdArgs fa, float* __restrict__ z, int N, int H, int W) {
+  constexpr int R0W = FP + 2, R0H = FH + 8, RA = FH + 6, RB = FH + 4;
+  // operands of a region's last columns reach two pixels past its last row
+  __shared__ __align__(256) uint4 ra[4 * RA * FP + 2];   // layer 1's output, then layer 3's
+  __shared__ __align__(256) uint4 rb[4 * RB * FP + 2];   // the image patch, then layer 2's output
+  uint2* r0 = (uint2*)rb;
+  static_assert(R0H * R0W * sizeof(uint2) <= sizeof rb, "the image patch lies in layer 2's region");
   const int nbx = (W + FW - 1) / FW, nby = (H + FH - 1) / FH;
   const int bx = blockIdx.x % nbx, by = (blockIdx.x / nbx) % nby, n = blockIdx.x / (nbx * nby);
   const int y0 = by * FH, x0 = bx * FW;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  // the four weight matrices, one after the other
-  for (int i = tid; i < kWAll / 8; i += 64 * FWAVES) {
-    const int e = i * 8;
-    const uint16_t* src = e < kW1 ? fa.w[0] + e
-                        : e < kW1 + kW2 ? fa.w[1] + (e - kW1)
-                        : e < kW1 + 2 * kW2 ? fa.w[2] + (e - kW1 - kW2)
-                        : fa.w[3] + (e - kW1 - 2 * kW2);
-    *(uint4*)(wl + e) = *(const uint4*)src;
-  }
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  FwdW<1> w1;
+  w1.load(fa, lane);
   // the image patch: the tile grown by four pixels, zero outside the image
   for (int p = tid; p < R0H * R0W; p += 64 * FWAVES) {
     const int r = p / R0W, c = p - r * R0W;
@@ -562,14 +598,20 @@ __global__ __launch_bounds__(64 * FWAVES) void k_forward(const uint16_t* __restr
     if (gy >= 0 && gy < H && gx >= 0 && gx < W) v = *(const uint2*)(x + ((size_t)(n * H + gy) * W + gx) * 4);
     r0[p] = v;
   }
-  __syncthreads();
-  fwd_layer<1, KEEP>(r0, ra, wl, fa.b[0], fa.act[0], z, n, H, W, y0, x0, wave, lane);
-  __syncthreads();
-  fwd_layer<2, KEEP>(ra, rb, wl + kW1, fa.b[1], fa.act[1], z, n, H, W, y0, x0, wave, lane);
-  __syncthreads();
-  fwd_layer<3, KEEP>(rb, ra, wl + kW1 + kW2, fa.b[2], fa.act[2], z, n, H, W, y0, x0, wave, lane);
-  __syncthreads();
-  fwd_layer<4, KEEP>(ra, nullptr, wl + kW1 + 2 * kW2, fa.b[3], nullptr, z, n, H, W, y0, x0, wave, lane);
+  lds_sync();
+  fwd_layer<1, KEEP>(w1, r0, ra, fa.act[0], z, n, H, W, y0, x0, wave, lane);
+  FwdW<2> w2;
+  w2.load(fa, lane);
+  lds_sync();
+  fwd_layer<2, KEEP>(w2, ra, rb, fa.act[1], z, n, H, W, y0, x0, wave, lane);
+  FwdW<3> w3;
+  w3.load(fa, lane);
+  lds_sync();
+  fwd_layer<3, KEEP>(w3, rb, ra, fa.act[2], z, n, H, W, y0, x0, wave, lane);
+  FwdW<4> w4;
+  w4.load(fa, lane);
+  lds_sync();
+  fwd_layer<4, KEEP>(w4, ra, nullptr, nullptr, z, n, H, W, y0, x0, wave, lane);
 }
 
 // MSE of y = x + z against t (three channels): dL/dz = 2 (y - t) / count as
@@ -622,16 +664,20 @@ struct Layer {
 };
 constexpr int kLayers = 4;
 
-// bfloat16 weights for the forward convolutions ([coutp][kpad32(cinm)], zero
-// padded) and, for layers 1..3, for the backward convolutions: the kernel
-// flipped and transposed, W'[i][2-ky][2-kx][o] = W[o][ky][kx][i], laid out
-// for a convolution from the layer's output channels to its input channels.
+// bfloat16 weights, zero padded.  Forward convolutions: in the order of the
+// MFMA operands, [K step][16-channel block][lane][8], lane l holding output
+// channel l % 16 at K positions 8 (l / 16) .. + 7 of the step (K = tap-major
+// taps x input channels).  Backward convolutions of layers 1..3: the kernel
+// flipped and transposed, W'[i][2-ky][2-kx][o] = W[o][ky][kx][i], as
+// [i][kpad32(taps x o)] for a convolution from the layer's output channels to
+// its input channels.
 __device__ __forceinline__ void prep_one(const float* __restrict__ params, uint16_t* __restrict__ wf,
                                          uint16_t* __restrict__ wb, const Layer& L, bool is_fwd, int idx) {
   if (is_fwd) {
-    const int KP = kpad32(L.cinm);
-    if (idx >= L.coutp * KP) return;
-    const int o = idx / KP, k = idx - o * KP, tap = k / L.cinm, i = k - tap * L.cinm;
+    if (idx >= L.coutp * kpad32(L.cinm)) return;
+    const int lane = (idx >> 3) & 63, op = idx >> 9, nbs = L.coutp / 16, ks = op / nbs, nb = op - ks * nbs;
+    const int o = nb * 16 + (lane & 15), k = ks * 32 + 8 * (lane >> 4) + (idx & 7);
+    const int tap = k / L.cinm, i = k - tap * L.cinm;
     float v = 0.f;
     if (o < L.coutr && tap < 9 && i < L.cinr) v = params[L.w_off + (o * 9 + tap) * L.cinr + i];
     wf[idx] = f2bf(v);
@@ -935,6 +981,7 @@ extern "C" wv_status wv_cnn_get_params(wv_cnn* net, float* host_params, hipStrea
 }
 
 static int conv_grid(int n, int h, int w) { return n * ((h + CH - 1) / CH) * ((w + CW - 1) / CW); }
+static int fwd_grid(int n, int h, int w) { return n * ((h + FH - 1) / FH) * ((w + FW - 1) / FW); }
 static int wgrad_blocks(int n, int h, int w) { return n * ((h + BH - 1) / BH) * ((w + BW - 1) / BW); }
 
 // The forward pass in one launch; keep: write the activations the backward
@@ -955,7 +1002,7 @@ static wv_status forward(wv_cnn* net, const uint16_t* x, int32_t n, int32_t h, i
     fa.b[i] = net->params + L[i].b_off;
   }
   for (int i = 0; i < 3; ++i) fa.act[i] = net->act[i];
-  const dim3 g(conv_grid(n, h, w)), b(64 * FWAVES);
+  const dim3 g(fwd_grid(n, h, w)), b(64 * FWAVES);
   if (keep)
     hipLaunchKernelGGL(k_forward<true>, g, b, 0, s, x, fa, zo, n, h, w);
   else
