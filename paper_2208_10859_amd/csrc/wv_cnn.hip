@@ -44,8 +44,7 @@ constexpr int kpad16(int cin) { return (9 * cin + 15) / 16 * 16; }
 // pairing of K positions works as long as A and B use the same one), and
 // receives D[4 (l / 16) + q][l % 16]: four consecutive output channels of
 // one pixel, stored as one 8-byte write.
-// A workgroup computes a 16 x 32 pixel block; wave w owns rows 4w .. 4w+3
-// (eight 16-pixel blocks).  Each wave holds the layer's whole weight matrix
+// A workgroup computes a 16 x 32 pixel block; wave w owns rows 4w .. 4w+3.  Each wave holds the layer's whole weight matrix
 // in registers (18 operands of 8 bf16 for 32 -> 32), loaded once; the input
 // patch with its one-pixel border is staged in LDS, for 32 channels as four
 // planes of 8-channel (16-byte) pixels so that the 16 lanes of an operand
@@ -130,53 +129,80 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
   __syncthreads();
 
-  f4 acc[8][NB];
+  // Wave w's rows 4 w .. 4 w + 3, one 16-column block after the other; the
+  // mask's words arrive while the products run.
+  uint2 mask[2][4][NB];
 #pragma unroll
-  for (int mb = 0; mb < 8; ++mb)
+  for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int r = 0; r < 4; ++r) {
+      const int gy = y0 + 4 * wave + r, gx = x0 + cb * 16 + i16;
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-    for (int mb = 0; mb < 8; ++mb) {
-      const int r = 4 * wave + (mb >> 1), c = (mb & 1) * 16 + i16;
-      uint4 bv;
-      if constexpr (CIN == 32) {
-        const int ky = ks / 3, kx = ks - 3 * (ks / 3);
-        bv = ((const uint4*)lds)[g * PLANE + (r + ky) * PW + c + kx];
-      } else {
-        // taps t0 = 8 ks + 2 g and t0 + 1, four channels each; taps >= 9 are zero
-        const uint2* p8 = (const uint2*)lds;
-        const int t0 = ks * 8 + 2 * g, t1 = t0 + 1;
-        const int u0 = min(t0, 8), u1 = min(t1, 8);
-        uint2 lo = p8[(r + u0 / 3) * PW + c + u0 % 3];
-        uint2 hi = p8[(r + u1 / 3) * PW + c + u1 % 3];
-        if (t0 >= 9) lo = make_uint2(0u, 0u);
-        if (t1 >= 9) hi = make_uint2(0u, 0u);
-        bv = make_uint4(lo.x, lo.y, hi.x, hi.y);
+      for (int nb = 0; nb < NB; ++nb) {
+        mask[cb][r][nb] = make_uint2(0u, 0u);
+        if (gy < H && gx < W)
+          mask[cb][r][nb] = *(const uint2*)(aux + ((size_t)(n * H + gy) * W + gx) * COUT + nb * 16 + 4 * g);
       }
-      const bf8 b = as_bf8(bv);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[ks][nb], b, acc[mb][nb], 0, 0, 0);
     }
-  }
-
-  // epilogue: lane (g, i16) holds channels nb * 16 + 4 g .. + 3 of pixel i16
 #pragma unroll
-  for (int mb = 0; mb < 8; ++mb) {
-    const int gy = y0 + 4 * wave + (mb >> 1), gx = x0 + (mb & 1) * 16 + i16;
-    if (gy >= H || gx >= W) continue;
-    const size_t px = (size_t)(n * H + gy) * W + gx;
+  for (int cb = 0; cb < 2; ++cb) {
+    f4 acc[4][NB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const size_t o = px * COUT + nb * 16 + 4 * g;
-      const uint2 m = *(const uint2*)(aux + o);
-      const uint16_t mh[4] = {(uint16_t)m.x, (uint16_t)(m.x >> 16), (uint16_t)m.y, (uint16_t)(m.y >> 16)};
-      float r[4];
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) r[q] = bf2f(mh[q]) > 0.f ? acc[mb][nb][q] : 0.f;
-      *(uint2*)(out + o) = make_uint2(pk_bf16(r[0], r[1]), pk_bf16(r[2], r[3]));
+      for (int nb = 0; nb < NB; ++nb) acc[r][nb] = f4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (CIN == 32) {
+      // an input row's operand serves the three output rows it reaches (per
+      // output the taps come in the order (ky, kx))
+      const uint4* p = (const uint4*)lds + g * PLANE + 4 * wave * PW + cb * 16 + i16;
+#pragma unroll
+      for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+          const bf8 b = as_bf8(p[i * PW + kx]);
+#pragma unroll
+          for (int ky = 0; ky < 3; ++ky) {
+            const int r = i - ky;
+            if (r < 0 || r >= 4) continue;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+              acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[ky * 3 + kx][nb], b, acc[r][nb], 0, 0, 0);
+          }
+        }
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          // taps t0 = 8 ks + 2 g and t0 + 1, four channels each; taps >= 9 are zero
+          const uint2* p8 = (const uint2*)lds + (4 * wave + r) * PW + cb * 16 + i16;
+          const int t0 = ks * 8 + 2 * g, t1 = t0 + 1;
+          const int u0 = min(t0, 8), u1 = min(t1, 8);
+          uint2 lo = p8[(u0 / 3) * PW + u0 % 3];
+          uint2 hi = p8[(u1 / 3) * PW + u1 % 3];
+          if (t0 >= 9) lo = make_uint2(0u, 0u);
+          if (t1 >= 9) hi = make_uint2(0u, 0u);
+          const bf8 b = as_bf8(make_uint4(lo.x, lo.y, hi.x, hi.y));
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[ks][nb], b, acc[r][nb], 0, 0, 0);
+        }
+    }
+    // epilogue: lane (g, i16) holds channels nb * 16 + 4 g .. + 3 of pixel i16
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int gy = y0 + 4 * wave + r, gx = x0 + cb * 16 + i16;
+      if (gy >= H || gx >= W) continue;
+      const size_t px = (size_t)(n * H + gy) * W + gx;
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const uint2 m = mask[cb][r][nb];
+        const uint16_t mh[4] = {(uint16_t)m.x, (uint16_t)(m.x >> 16), (uint16_t)m.y, (uint16_t)(m.y >> 16)};
+        float v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = bf2f(mh[q]) > 0.f ? acc[r][nb][q] : 0.f;
+        *(uint2*)(out + px * COUT + nb * 16 + 4 * g) = make_uint2(pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3]));
+      }
     }
   }
 }
@@ -184,29 +210,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // Weight and bias gradients of one layer: dW[o][tap][i] = sum over pixels of
 // dy[p][o] x[p + tap offset][i], as a GEMM with M = output channels, N = 9
 // taps x input channels (padded to 16), K = pixels, on
-// v_mfma_f32_16x16x32_bf16 (operand layout as in k_conv).  A workgroup stages the transposed dy of
-// an 8 x 32 block and three column-shifted, channel-major copies of the input
-// patch (so that four consecutive pixels of an operand are one aligned 8-byte
-// read), loops over `bpw` blocks, then adds its partial sums atomically.
-//   CINM / CINR: input channels in memory / real; DYC: dy channels in memory;
-//   COUTP / COUTR: output channels padded to 16 / real.
-template <int CINM, int CINR, int DYC, int COUTP, int COUTR>
-__global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ x,
+// v_mfma_f32_16x16x32_bf16 (operand layout as in k_conv).  This kernel: the
+// first layer (image with 4 channels in memory, 3 real, dy with 32).  A
+// workgroup stages the transposed dy of an 8 x 32 block and three
+// column-shifted, channel-major copies of the input patch (so that four
+// consecutive pixels of an operand are one aligned 8-byte read), and loops
+// over `bpw` blocks.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad(const uint16_t* __restrict__ x,
                                                const uint16_t* __restrict__ dy,
-                                               float* __restrict__ part, int N, int H, int W, int bpw) {
-  constexpr int KN = kpad16(CINM), MB = COUTP / 16, NB = KN / 16;
+                                               float* __restrict__ part, int width, int N, int H, int W,
+                                               int bpw) {
+  constexpr int CINM = 4, CINR = 3, COUTR = HID;
+  constexpr int KN = kpad16(CINM), MB = COUTR / 16, NB = KN / 16;
   constexpr int NW = COUTR * 9 * CINR;     // weights of the layer; its COUTR biases follow
   constexpr int PR = BH + 2;
   // wave w computes the 16-column blocks nb = w, w + 4, ... of the result for
   // every 16-channel block mb: one x operand read serves MB products
   constexpr int PER_WAVE = (NB + 3) / 4;
-  static_assert(MB <= 2, "at most 32 output channels");
   // Row strides padded by 8 values: unpadded (512 and 640 bytes) the 16 rows
   // of one operand read started on 1 or 2 distinct 16-byte bank groups (16-
   // and 8-fold conflicts); 528 and 656 bytes spread them over all 16.
   constexpr int DS = BH * BW + 8;          // dyt: one output channel
   constexpr int XS = PR * BW + 8;          // xs: one (column shift, input channel) plane
-  __shared__ __align__(16) uint16_t dyt[COUTP * DS];
+  __shared__ __align__(16) uint16_t dyt[COUTR * DS];
   __shared__ __align__(16) uint16_t xs[3 * CINM * XS];
   const int nbx = (W + BW - 1) / BW, nby = (H + BH - 1) / BH, nblocks = nbx * nby * N;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i16 = lane & 15, g4 = lane >> 4;
@@ -216,85 +242,65 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ x,
 #pragma unroll
     for (int m = 0; m < MB; ++m) acc[k][m] = f4{0.f, 0.f, 0.f, 0.f};
   // bias gradient: per-thread partial sums of the dy channels this thread
-  // loads (channels 8 (tid & 3) .. + 7 for 32-channel dy, 0 .. 3 for 4)
+  // loads (channels 8 (tid & 3) .. + 7)
   float bpart[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) bpart[j] = 0.f;
-  if constexpr (DYC == 4) {
-    // rows of the output channels beyond the four in memory stay zero
-    for (int idx = 4 * DS + tid; idx < COUTP * DS; idx += 256) dyt[idx] = 0;
-  }
-  for (int bi = 0; bi < bpw; ++bi) {
-    const int blk = blockIdx.x * bpw + bi;
-    if (blk >= nblocks) break;
+  // dy: 16-byte (8-channel) pixel pieces, zero outside the image, two
+  // horizontally adjacent pixels per item; x: the patch of the block grown by
+  // one pixel (34 columns), 8-byte pixels in pairs.
+  constexpr int DYI = BH * BW / 2 * 4, NDY = (DYI + 255) / 256;
+  constexpr int NPR = (BW + 2) / 2;          // column pairs per patch row
+  constexpr int XI = PR * NPR, NXI = (XI + 255) / 256;
+  uint4 dv[NDY][2];
+  uint2 xv[NXI][2];
+  // A block's global reads go into registers ahead of its turn, while the
+  // block before is multiplied: the staging waits for no memory.
+  auto load = [&](int blk) __attribute__((always_inline)) {
     const int bx = blk % nbx, by = (blk / nbx) % nby, n = blk / (nbx * nby);
-    // Every global read of the block is issued first, into registers (while
-    // the previous block's products may still read LDS), and the LDS writes
-    // follow: the staging waits for memory once per block instead of once per
-    // loop iteration.
-    // dy: 16-byte (8-channel) or 8-byte (4-channel) pixel pieces, zero outside
-    // the image, two horizontally adjacent pixels per item
-    constexpr int DYI = DYC == 32 ? BH * BW / 2 * 4 : BH * BW / 2, NDY = (DYI + 255) / 256;
-    uint4 dv[NDY][2];
 #pragma unroll
     for (int it = 0; it < NDY; ++it) {
       const int idx = tid + 256 * it;
-      const int pp = DYC == 32 ? idx >> 2 : idx, ch = DYC == 32 ? idx & 3 : 0;
+      const int pp = idx >> 2, ch = idx & 3;
       const int gy = by * BH + (2 * pp) / BW;
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         const int gx = bx * BW + (2 * pp) % BW + hh;
         dv[it][hh] = make_uint4(0u, 0u, 0u, 0u);
-        if (idx < DYI && gy < H && gx < W) {
-          if constexpr (DYC == 32) {
-            dv[it][hh] = *(const uint4*)(dy + ((size_t)(n * H + gy) * W + gx) * 32 + ch * 8);
-          } else {
-            const uint2 v = *(const uint2*)(dy + ((size_t)(n * H + gy) * W + gx) * 4);
-            dv[it][hh] = make_uint4(v.x, v.y, 0u, 0u);
-          }
-        }
+        if (idx < DYI && gy < H && gx < W)
+          dv[it][hh] = *(const uint4*)(dy + ((size_t)(n * H + gy) * W + gx) * 32 + ch * 8);
       }
     }
-    // x: the patch of the block grown by one pixel (34 columns), the same
-    // pieces, two horizontally adjacent pixels per item
-    constexpr int XC = CINM == 32 ? 4 : 1;     // 16- or 8-byte pieces per pixel
-    constexpr int NPR = (BW + 2) / 2;          // column pairs per patch row
-    constexpr int XI = PR * NPR * XC, NXI = (XI + 255) / 256;
-    uint4 xv[NXI][2];
 #pragma unroll
     for (int it = 0; it < NXI; ++it) {
       const int idx = tid + 256 * it;
-      const int q = idx / XC, ch = idx - q * XC;
-      const int r = q / NPR, m = q - r * NPR;
+      const int r = idx / NPR, m = idx - r * NPR;
       const int gy = by * BH + r - 1;
 #pragma unroll
       for (int hh = 0; hh < 2; ++hh) {
         const int gx = bx * BW + 2 * m + hh - 1;
-        xv[it][hh] = make_uint4(0u, 0u, 0u, 0u);
-        if (idx < XI && gy >= 0 && gy < H && gx >= 0 && gx < W) {
-          if constexpr (CINM == 32) {
-            xv[it][hh] = *(const uint4*)(x + ((size_t)(n * H + gy) * W + gx) * 32 + ch * 8);
-          } else {
-            const uint2 v = *(const uint2*)(x + ((size_t)(n * H + gy) * W + gx) * 4);
-            xv[it][hh] = make_uint4(v.x, v.y, 0u, 0u);
-          }
-        }
+        xv[it][hh] = make_uint2(0u, 0u);
+        if (idx < XI && gy >= 0 && gy < H && gx >= 0 && gx < W)
+          xv[it][hh] = *(const uint2*)(x + ((size_t)(n * H + gy) * W + gx) * 4);
       }
     }
+  };
+  const int blk0 = blockIdx.x * bpw, blk1 = min(blk0 + bpw, nblocks);
+  load(blk0);
+  for (int blk = blk0; blk < blk1; ++blk) {
     __syncthreads();   // the previous block's reads of dyt and xs are done
     // dy transposed, dyt[o][r * 32 + c], a 4-byte word per pixel pair
 #pragma unroll
     for (int it = 0; it < NDY; ++it) {
       const int idx = tid + 256 * it;
       if (idx >= DYI) break;
-      const int pp = DYC == 32 ? idx >> 2 : idx, ch = DYC == 32 ? idx & 3 : 0;
+      const int pp = idx >> 2, ch = idx & 3;
       const uint32_t w0[4] = {dv[it][0].x, dv[it][0].y, dv[it][0].z, dv[it][0].w};
       const uint32_t w1[4] = {dv[it][1].x, dv[it][1].y, dv[it][1].z, dv[it][1].w};
 #pragma unroll
-      for (int j = 0; j < (DYC == 32 ? 8 : 4); ++j) {
-        const bool real = DYC == 32 || j < COUTR;
-        const uint32_t h0 = real ? (w0[j >> 1] >> (16 * (j & 1))) & 0xffffu : 0u;
-        const uint32_t h1 = real ? (w1[j >> 1] >> (16 * (j & 1))) & 0xffffu : 0u;
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t h0 = (w0[j >> 1] >> (16 * (j & 1))) & 0xffffu;
+        const uint32_t h1 = (w1[j >> 1] >> (16 * (j & 1))) & 0xffffu;
         *(uint32_t*)(dyt + (ch * 8 + j) * DS + 2 * pp) = h0 | (h1 << 16);
         bpart[j] += bf2f((uint16_t)h0) + bf2f((uint16_t)h1);
       }
@@ -307,15 +313,14 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ x,
     for (int it = 0; it < NXI; ++it) {
       const int idx = tid + 256 * it;
       if (idx >= XI) break;
-      const int q = idx / XC, ch = idx - q * XC;
-      const int r = q / NPR, m = q - r * NPR;
-      const uint32_t w0[4] = {xv[it][0].x, xv[it][0].y, xv[it][0].z, xv[it][0].w};
-      const uint32_t w1[4] = {xv[it][1].x, xv[it][1].y, xv[it][1].z, xv[it][1].w};
+      const int r = idx / NPR, m = idx - r * NPR;
+      const uint32_t w0[2] = {xv[it][0].x, xv[it][0].y};
+      const uint32_t w1[2] = {xv[it][1].x, xv[it][1].y};
 #pragma unroll
-      for (int j = 0; j < (CINM == 32 ? 8 : 4); ++j) {
+      for (int j = 0; j < 4; ++j) {
         const uint32_t h0 = (w0[j >> 1] >> (16 * (j & 1))) & 0xffffu;
         const uint32_t h1 = (w1[j >> 1] >> (16 * (j & 1))) & 0xffffu;
-        const int i = ch * 8 + j, row = r * BW + 2 * m;
+        const int i = j, row = r * BW + 2 * m;
         if (m < NPR - 1) {
           *(uint32_t*)(xs + i * XS + row) = h0 | (h1 << 16);
           xs[(CINM + i) * XS + row] = (uint16_t)h1;
@@ -327,6 +332,7 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ x,
       }
     }
     __syncthreads();
+    if (blk + 1 < blk1) load(blk + 1);
     // K steps of 32 pixels: one block row each, lane group g4 taking
     // columns 8 g4 .. 8 g4 + 7 of both operands
 #pragma unroll 1
@@ -352,9 +358,9 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ x,
       }
     }
   }
-  // this workgroup's partial sums, plain stores into its row of `part`
-  // (parameter layout: dW, then db); k_wsum adds the rows up
-  float* row_out = part + (size_t)blockIdx.x * (NW + COUTR);
+  // this workgroup's partial sums, plain stores into its row of `part` (rows
+  // of `width` values; parameter layout: dW, then db); k_wsum adds the rows up
+  float* row_out = part + (size_t)blockIdx.x * width;
 #pragma unroll
   for (int k = 0; k < PER_WAVE; ++k) {
     const int nb = wave + 4 * k;
@@ -371,39 +377,213 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ x,
   }
   // bias gradient: lanes holding the same channels, then the four waves
   __shared__ float bred[4][32];
-  if constexpr (DYC == 32) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+  for (int j = 0; j < 8; ++j)
 #pragma unroll
-      for (int m = 4; m < 64; m <<= 1) bpart[j] += __shfl_xor(bpart[j], m);
-    if (lane < 4)
+    for (int m = 4; m < 64; m <<= 1) bpart[j] += __shfl_xor(bpart[j], m);
+  if (lane < 4)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) bred[wave][lane * 8 + j] = bpart[j];
-  } else {
-#pragma unroll
-    for (int j = 0; j < COUTR; ++j)
-#pragma unroll
-      for (int m = 1; m < 64; m <<= 1) bpart[j] += __shfl_xor(bpart[j], m);
-    if (lane == 0)
-#pragma unroll
-      for (int j = 0; j < COUTR; ++j) bred[wave][j] = bpart[j];
-  }
+    for (int j = 0; j < 8; ++j) bred[wave][lane * 8 + j] = bpart[j];
   __syncthreads();
   if (tid < COUTR) row_out[NW + tid] = bred[0][tid] + bred[1][tid] + bred[2][tid] + bred[3][tid];
 }
 
-// Sum of the weight-gradient kernel's per-workgroup rows into the gradient
-// (zeroed before): thread j of column block x adds rows 32 y .. 32 y + 31 of
-// parameter j, one atomic per 32 rows.
-__global__ __launch_bounds__(256) void k_wsum(const float* __restrict__ part, int rows, int width,
-                                              float* __restrict__ g) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= width) return;
-  const int r0 = blockIdx.y * 32, r1 = min(r0 + 32, rows);
+// Weight and bias gradients of the layers with 32 input channels, the same
+// GEMM.  Both operands are channels x pixels, the transpose of what memory
+// holds; the staged pixels stay as they are, [16-channel half][pixel][16], and
+// the operands are read with the LDS's transposing read
+// (ds_read_b64_tr_b16: of 16 lanes, lane s addresses 4 channels of a pixel,
+// pixel s / 4, channels 4 (s % 4) .. + 3, and receives channel s of the four
+// pixels), two per operand.  A workgroup stages 16 x 32 pixel blocks, the next
+// one's global reads under way while one is multiplied.  Wave w takes input
+// channels 16 (w % 2) .. and four rows of the block, and streams down the x
+// rows: an x operand serves the three taps (ky) that reach the wave's dy rows,
+// which stay in registers.  The bias gradient is the product with a column of
+// ones.  The four waves of a channel half are summed in LDS at the end.
+// What bounds it: the latency of its two rounds of global reads, then their
+// bytes.  16 x 128 x 128, 32 dy channels: 19.4 -> 14.7 us (33.5 MB, 6.5 us at a
+// copy's rate), 3 dy channels: 14.9 -> 12.4 us, against transposed copies
+// written to LDS a word at a time.  Reads two blocks ahead: 16.2.
+//   DYC: dy channels in memory (32, or 4 of which 3 are real).
+constexpr int GH = 16, GW = 32;           // block of pixels
+constexpr int GWAVES = 8;
+typedef short s4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ bf8 tr_operand(const uint16_t* p) {
+  using LP = __attribute__((address_space(3))) s4*;
+  const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LP)(p));
+  const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LP)(p + 16 * 16));   // 16 pixels on
+  return as_bf8(__builtin_bit_cast(uint4, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7)));
+}
+
+template <int DYC>
+__global__ __launch_bounds__(64 * GWAVES) __attribute__((amdgpu_waves_per_eu(2)))
+void k_wgrad32(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, float* __restrict__ part, int width,
+               int N, int H, int W, int bpw) {
+  constexpr int MB = DYC == 32 ? 2 : 1, COUTR = DYC == 32 ? 32 : 3, NW = COUTR * 9 * 32, NT = 64 * GWAVES;
+  constexpr int XPX = (GH + 2) * (GW + 2), DPX = GH * GW;      // staged pixels
+  constexpr int NACC = 9 * MB + MB;                             // accumulator tiles of a wave
+  constexpr int STAGE = (2 * XPX + MB * DPX) * 16 * 2, REDUCE = GWAVES / 2 * NACC * 64 * 16;
+  __shared__ __align__(16) unsigned char lds[STAGE > REDUCE ? STAGE : REDUCE];
+  uint16_t* xs = (uint16_t*)lds;               // [2][XPX][16]
+  uint16_t* ds = xs + 2 * XPX * 16;            // [MB][DPX][16]
+  const int nbx = (W + GW - 1) / GW, nby = (H + GH - 1) / GH, nblocks = nbx * nby * N;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int i16 = lane & 15, g = lane >> 4, ib = wave & 1, rq = wave >> 1;
+  // this lane's part of an operand's first 16 pixels
+  const int tr = (4 * g + (i16 >> 2)) * 16 + 4 * (i16 & 3);
+
+  constexpr int NX = (XPX * 4 + NT - 1) / NT, ND = DYC == 32 ? DPX * 4 / NT : (DPX + NT - 1) / NT;
+  uint4 xv[NX], dv[ND];
+  auto load = [&](int blk) __attribute__((always_inline)) {
+    const int bx = blk % nbx, by = (blk / nbx) % nby, n = blk / (nbx * nby);
+#pragma unroll
+    for (int it = 0; it < NX; ++it) {
+      const int idx = tid + NT * it, px = idx >> 2, r = px / (GW + 2), c = px - r * (GW + 2);
+      const int gy = by * GH + r - 1, gx = bx * GW + c - 1;
+      xv[it] = make_uint4(0u, 0u, 0u, 0u);
+      if (idx < XPX * 4 && gy >= 0 && gy < H && gx >= 0 && gx < W)
+        xv[it] = *(const uint4*)(x + ((size_t)(n * H + gy) * W + gx) * 32 + (idx & 3) * 8);
+    }
+#pragma unroll
+    for (int it = 0; it < ND; ++it) {
+      const int idx = tid + NT * it, px = DYC == 32 ? idx >> 2 : idx;
+      const int gy = by * GH + px / GW, gx = bx * GW + px % GW;
+      dv[it] = make_uint4(0u, 0u, 0u, 0u);
+      if (px < DPX && gy < H && gx < W) {
+        const size_t e = (size_t)(n * H + gy) * W + gx;
+        if constexpr (DYC == 32) {
+          dv[it] = *(const uint4*)(dy + e * 32 + (idx & 3) * 8);
+        } else {
+          const uint2 v = *(const uint2*)(dy + e * 4);
+          dv[it] = make_uint4(v.x, v.y & 0xffffu, 0u, 0u);   // three real channels
+        }
+      }
+    }
+  };
+
+  f4 acc[9][MB], accb[MB];
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+    accb[m] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t][m] = f4{0.f, 0.f, 0.f, 0.f};
+  }
+  const uint32_t one2 = 0x3f803f80u;
+  const bf8 ones = as_bf8(make_uint4(one2, one2, one2, one2));
+  const int blk0 = blockIdx.x * bpw, blk1 = min(blk0 + bpw, nblocks);
+  load(blk0);
+  for (int blk = blk0; blk < blk1; ++blk) {
+    if (blk > blk0) __syncthreads();   // the previous block's operands are read
+#pragma unroll
+    for (int it = 0; it < NX; ++it) {
+      const int idx = tid + NT * it;
+      if (idx < XPX * 4) *(uint4*)(xs + ((idx & 3) >> 1) * (XPX * 16) + (idx >> 2) * 16 + (idx & 1) * 8) = xv[it];
+    }
+#pragma unroll
+    for (int it = 0; it < ND; ++it) {
+      const int idx = tid + NT * it;
+      if constexpr (DYC == 32) {
+        *(uint4*)(ds + ((idx & 3) >> 1) * (DPX * 16) + (idx >> 2) * 16 + (idx & 1) * 8) = dv[it];
+      } else if (idx < DPX) {
+        *(uint4*)(ds + idx * 16) = dv[it];
+        *(uint4*)(ds + idx * 16 + 8) = make_uint4(0u, 0u, 0u, 0u);
+      }
+    }
+    __syncthreads();
+    if (blk + 1 < blk1) load(blk + 1);
+    bf8 a[4][MB];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int m = 0; m < MB; ++m) a[r][m] = tr_operand(ds + (m * DPX + (4 * rq + r) * GW) * 16 + tr);
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+      for (int kx = 0; kx < 3; ++kx) {
+        const bf8 b = tr_operand(xs + (ib * XPX + (4 * rq + i) * (GW + 2) + kx) * 16 + tr);
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) {
+          const int r = i - ky;
+          if (r < 0 || r >= 4) continue;
+#pragma unroll
+          for (int m = 0; m < MB; ++m)
+            acc[ky * 3 + kx][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r][m], b, acc[ky * 3 + kx][m], 0, 0, 0);
+        }
+      }
+    if (ib == 0)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r][m], ones, accb[m], 0, 0, 0);
+  }
+  // the four row quarters of each channel half: 1 into 0 and 3 into 2, then 2 into 0
+  f4* red = (f4*)lds;
+#pragma unroll
+  for (int step = 1; step <= 2; ++step) {
+    __syncthreads();
+    const bool gives = step == 1 ? rq & 1 : rq == 2, takes = step == 1 ? !(rq & 1) : rq == 0;
+    f4* slot = red + (size_t)((rq >> 1) * 2 + ib) * NACC * 64 + lane;    // of the pair (rq, rq ^ 1)
+    f4* from = step == 1 ? slot : red + (size_t)ib * NACC * 64 + lane;
+    if (gives) {
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) from[(t * MB + m) * 64] = acc[t][m];
+#pragma unroll
+      for (int m = 0; m < MB; ++m) from[(9 * MB + m) * 64] = accb[m];
+    }
+    __syncthreads();
+    if (takes) {
+#pragma unroll
+      for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int m = 0; m < MB; ++m) acc[t][m] += from[(t * MB + m) * 64];
+#pragma unroll
+      for (int m = 0; m < MB; ++m) accb[m] += from[(9 * MB + m) * 64];
+    }
+  }
+  if (rq) return;
+  // this workgroup's row of `part` (width values; dW, then db): lane (g, i16)
+  // holds output channels 4 g .. + 3 of input channel i16
+  float* row_out = part + (size_t)blockIdx.x * width;
+#pragma unroll
+  for (int m = 0; m < MB; ++m)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int o = m * 16 + 4 * g + q;
+      if (o >= COUTR) continue;
+#pragma unroll
+      for (int t = 0; t < 9; ++t) row_out[(o * 9 + t) * 32 + ib * 16 + i16] = acc[t][m][q];
+      if (ib == 0 && i16 == 0) row_out[NW + o] = accb[m][q];
+    }
+}
+
+// Sum of the weight-gradient kernels' per-workgroup rows, every layer at once:
+// a workgroup adds 64 parameters, each of its eight waves every eighth row,
+// and writes the gradient (and the caller's copy) in a fixed order.
+// What bounds it: the rows' bytes.  One launch per
+// layer with atomics into a cleared gradient, and a copy of it, took
+// 4 x 4.5 + 8 us of a 16 x 128 x 128 step; this one takes 7 us (26 MB).
+// rows0: rows of the parameters below `first` (the first layer's), rows: of the
+// others.
+__global__ __launch_bounds__(512) void k_wsum(const float* __restrict__ part, int rows0, int first, int rows,
+                                              int width, float* __restrict__ g, float* __restrict__ g2) {
+  __shared__ float red[8][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.x * 64 + lane;
   float s = 0.f;
+  if (j < width) {
+    const int n = j < first ? rows0 : rows;
 #pragma unroll 8
-  for (int r = r0; r < r1; ++r) s += part[(size_t)r * width + j];
-  atomicAdd(&g[j], s);
+    for (int r = wave; r < n; r += 8) s += part[(size_t)r * width + j];
+  }
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave || j >= width) return;
+#pragma unroll
+  for (int w = 1; w < 8; ++w) s += red[w][lane];
+  g[j] = s;
+  if (g2) g2[j] = s;
 }
 
 // The whole forward pass in one kernel (3 -> 32 -> 32 -> 32 -> 3): a
@@ -615,32 +795,63 @@ void k_forward(const uint16_t* __restrict__ x, const FwdArgs fa, float* __restri
 }
 
 // MSE of y = x + z against t (three channels): dL/dz = 2 (y - t) / count as
-// bfloat16, and the mean squared difference accumulated into *loss.
-__global__ __launch_bounds__(256) void k_loss(const float* __restrict__ z, const uint16_t* __restrict__ x,
-                                              const float* __restrict__ t, uint16_t* __restrict__ dz,
-                                              float* __restrict__ loss, int P, float scale,
-                                              float inv_count) {
-  __shared__ float red[256];
-  const int p = blockIdx.x * 256 + threadIdx.x;
+// bfloat16, and the mean squared difference in *loss.  Each workgroup leaves
+// its sum in part[]; the last one to finish (counter `done`, zero between
+// launches) adds them up in order.  One atomic per 256 pixels on one address,
+// with a clearing fill before and a copy after, took 15 + 8 us at
+// 16 x 128 x 128; this takes 6 us (12.6 MB; 512 workgroups: 15.7, the atomics
+// on one address take 30 ns each).
+constexpr int kLossGroups = 64, kLossThreads = 1024;
+struct __attribute__((packed, aligned(4))) F4u { float v[4]; };   // 4-byte aligned targets
+__global__ __launch_bounds__(kLossThreads) void k_loss(const float4* __restrict__ z, const uint2* __restrict__ x,
+                                              const F4u* __restrict__ t, uint2* __restrict__ dz,
+                                              float* __restrict__ part, uint32_t* __restrict__ done,
+                                              float* __restrict__ loss, int P, float scale, float inv_count) {
+  __shared__ float red[kLossThreads / 64];
+  __shared__ bool last;
   float s = 0.f;
-  if (p < P) {
+#pragma unroll 4
+  for (int p = blockIdx.x * kLossThreads + threadIdx.x; p < P; p += gridDim.x * kLossThreads) {
+    const float4 zv = z[p];
+    const uint2 xv = x[p];
+    const F4u tv = t[p];
+    const float zc[3] = {zv.x, zv.y, zv.z};
+    const uint16_t xc[3] = {(uint16_t)xv.x, (uint16_t)(xv.x >> 16), (uint16_t)xv.y};
+    uint32_t o[3];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      float d = 0.f;
-      if (c < 3) {
-        d = bf2f(x[p * 4 + c]) + z[p * 4 + c] - t[p * 4 + c];
-        s += d * d;
-      }
-      dz[p * 4 + c] = f2bf(scale * d);
+    for (int c = 0; c < 3; ++c) {
+      const float d = bf2f(xc[c]) + zc[c] - tv.v[c];
+      s += d * d;
+      o[c] = f2bf(scale * d);
     }
+    dz[p] = make_uint2(o[0] | (o[1] << 16), o[2]);
   }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+  auto block_sum = [&](float v) {
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m);
     __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    float t = red[0];
+#pragma unroll
+    for (int w = 1; w < kLossThreads / 64; ++w) t += red[w];
+    return t;
+  };
+  s = block_sum(s);
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&part[blockIdx.x], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
   }
-  if (threadIdx.x == 0) atomicAdd(loss, red[0] * inv_count);
+  __syncthreads();
+  if (!last) return;
+  s = 0.f;
+  for (int i = threadIdx.x; i < (int)gridDim.x; i += kLossThreads)
+    s += __hip_atomic_load(&part[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  s = block_sum(s);
+  if (threadIdx.x == 0) {
+    *loss = s * inv_count;
+    *done = 0u;
+  }
 }
 
 // Adam on the fp32 parameters.
@@ -824,9 +1035,9 @@ using namespace wv::cnn;
 using wvp::fail;
 using wvp::hip_fail;
 
-// weight gradients: at most this many workgroups, each writing one row of
-// partial sums
-constexpr int kWgradRows = 512;
+// weight gradients: at most this many workgroups (the first layer's kernel runs
+// two per CU, the others' one), each writing one row of partial sums
+constexpr int kWgradRows0 = 512, kWgradRows = 256;
 
 struct wv_cnn {
   Layer layer[kLayers];
@@ -845,12 +1056,13 @@ struct wv_cnn {
   uint16_t* dbuf[2] = {};       // [P][32]
   float* z = nullptr;           // [P][4]
   uint16_t* dz = nullptr;       // [P][4]
-  float* loss = nullptr;        // device scalar
+  float* loss_part = nullptr;   // loss sums, one per workgroup
+  uint32_t* loss_done = nullptr;  // workgroups finished (0 between launches)
   float* guard_abs = nullptr;   // per-tile guard sums
   int* guard_bad = nullptr;
   int* guard_use = nullptr;
   int* crops = nullptr;
-  float* wpart = nullptr;       // weight-gradient partial sums, [kWgradRows][largest layer]
+  float* wpart = nullptr;       // weight-gradient partial sums, [kWgradRows0][n_params]
   int n = 0, h = 0, w = 0;      // shape of the last forward
   bool fwd_valid = false, grad_valid = false;
   bool prepped = false;
@@ -883,7 +1095,7 @@ extern "C" wv_status wv_cnn_destroy(wv_cnn* net) {
   if (!net) return WV_OK;
   (void)hipDeviceSynchronize();
   void* ptrs[] = {net->params, net->grads, net->adam_m, net->adam_v, net->x, net->act[0], net->act[1],
-                  net->act[2], net->dbuf[0], net->dbuf[1], net->z, net->dz, net->loss, net->guard_abs,
+                  net->act[2], net->dbuf[0], net->dbuf[1], net->z, net->dz, net->loss_part, net->loss_done, net->guard_abs,
                   net->guard_bad, net->guard_use, net->crops, net->wpart};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -922,12 +1134,14 @@ extern "C" wv_status wv_cnn_create(wv_cnn** out, int64_t max_pixels) {
   for (int i = 0; i < 2; ++i) alloc((void**)&net->dbuf[i], P * HID * 2);
   alloc((void**)&net->z, P * 4 * 4);
   alloc((void**)&net->dz, P * 4 * 2);
-  alloc((void**)&net->loss, sizeof(float));
+  alloc((void**)&net->loss_part, kLossGroups * sizeof(float));
+  alloc((void**)&net->loss_done, sizeof(uint32_t));
   alloc((void**)&net->guard_abs, 65536 * sizeof(float));
   alloc((void**)&net->guard_bad, 65536 * sizeof(int));
   alloc((void**)&net->guard_use, 65536 * sizeof(int));
   alloc((void**)&net->crops, 3 * 4096 * sizeof(int));
-  alloc((void**)&net->wpart, (size_t)kWgradRows * (HID * 9 * HID + HID) * sizeof(float));
+  // a weight-gradient workgroup has at least one pixel
+  alloc((void**)&net->wpart, (size_t)std::min<int64_t>(kWgradRows0, max_pixels) * np);
   if (e != hipSuccess) {
     wv_cnn_destroy(net);
     return e == hipErrorOutOfMemory ? fail(WV_ENOMEM, "wv_cnn buffers: %s", hipGetErrorString(e))
@@ -982,7 +1196,6 @@ extern "C" wv_status wv_cnn_get_params(wv_cnn* net, float* host_params, hipStrea
 
 static int conv_grid(int n, int h, int w) { return n * ((h + CH - 1) / CH) * ((w + CW - 1) / CW); }
 static int fwd_grid(int n, int h, int w) { return n * ((h + FH - 1) / FH) * ((w + FW - 1) / FW); }
-static int wgrad_blocks(int n, int h, int w) { return n * ((h + BH - 1) / BH) * ((w + BW - 1) / BW); }
 
 // The forward pass in one launch; keep: write the activations the backward
 // pass reads.
@@ -1033,12 +1246,11 @@ extern "C" wv_status wv_cnn_loss_grad(wv_cnn* net, const float* t, float* loss, 
   if (!net || !t || !loss) return fail(WV_EINVAL, "wv_cnn_loss_grad: bad argument");
   if (!net->fwd_valid) return fail(WV_EINVAL, "wv_cnn_loss_grad: no forward pass to differentiate");
   const int P = net->n * net->h * net->w;
-  hipError_t e = hipMemsetAsync(net->loss, 0, sizeof(float), s);
-  if (e != hipSuccess) return hip_fail(e, "wv_cnn_loss_grad");
-  hipLaunchKernelGGL(k_loss, dim3((P + 255) / 256), dim3(256), 0, s, net->zout, net->xin, t, net->dz,
-                     net->loss, P, 2.0f / (3.0f * (float)P), 1.0f / (3.0f * (float)P));
-  e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(loss, net->loss, sizeof(float), hipMemcpyDeviceToDevice, s);
+  hipLaunchKernelGGL(k_loss, dim3(std::min((P + kLossThreads - 1) / kLossThreads, kLossGroups)),
+                     dim3(kLossThreads), 0, s,
+                     (const float4*)net->zout, (const uint2*)net->xin, (const F4u*)t, (uint2*)net->dz, net->loss_part,
+                     net->loss_done, loss, P, 2.0f / (3.0f * (float)P), 1.0f / (3.0f * (float)P));
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "wv_cnn_loss_grad");
   net->grad_valid = true;
   return WV_OK;
@@ -1049,43 +1261,34 @@ extern "C" wv_status wv_cnn_backward(wv_cnn* net, float* grads, hipStream_t s) {
   if (!net->grad_valid) return fail(WV_EINVAL, "wv_cnn_backward: no loss gradient");
   const int n = net->n, h = net->h, w = net->w;
   const Layer* L = net->layer;
-  hipError_t e = hipMemsetAsync(net->grads, 0, (size_t)net->n_params * 4, s);
-  if (e != hipSuccess) return hip_fail(e, "wv_cnn_backward");
   const dim3 g(conv_grid(n, h, w)), b(256);
-  const int nblocks = wgrad_blocks(n, h, w);
-  // split over pixels: at most kWgradRows workgroups, each writing a row of
-  // partial sums that k_wsum adds into the gradient
-  const int bpw = (nblocks + kWgradRows - 1) / kWgradRows;
-  const int rows = (nblocks + bpw - 1) / bpw;
-  const dim3 gw(rows);
-  auto wsum = [&](const Layer& l) {
-    const int width = l.coutr * 9 * l.cinr + l.coutr;
-    hipLaunchKernelGGL(k_wsum, dim3((width + 255) / 256, (rows + 31) / 32), b, 0, s, (const float*)net->wpart,
-                       rows, width, net->grads + l.w_off);
-  };
+  // split over pixels: at most kWgradRows (kWgradRows0 for the first layer)
+  // workgroups, each writing a row of partial sums that k_wsum adds up
+  const int nb0 = n * ((h + BH - 1) / BH) * ((w + BW - 1) / BW), nb = n * ((h + GH - 1) / GH) * ((w + GW - 1) / GW);
+  const int bpw0 = (nb0 + kWgradRows0 - 1) / kWgradRows0, bpw = (nb + kWgradRows - 1) / kWgradRows;
+  const int rows0 = (nb0 + bpw0 - 1) / bpw0, rows = (nb + bpw - 1) / bpw;
+  const dim3 gw(rows), bw(64 * GWAVES);
+  auto part = [&](int l) { return net->wpart + L[l].w_off; };
+  const int np = net->n_params;
   // layer 4: dW4 from a3 and dz; d3 = (W4' * dz) masked by a3 > 0
-  hipLaunchKernelGGL((k_wgrad<HID, HID, 4, 16, 3>), gw, b, 0, s, net->act[2], net->dz, net->wpart, n, h, w, bpw);
-  wsum(L[3]);
+  hipLaunchKernelGGL((k_wgrad32<4>), gw, bw, 0, s, net->act[2], net->dz, part(3), np, n, h, w, bpw);
   hipLaunchKernelGGL((k_conv<4, HID>), g, b, 0, s, net->dz, net->wb[3], net->act[2], net->dbuf[0], n, h, w);
   // layer 3
-  hipLaunchKernelGGL((k_wgrad<HID, HID, HID, HID, HID>), gw, b, 0, s, net->act[1], net->dbuf[0], net->wpart,
-                     n, h, w, bpw);
-  wsum(L[2]);
+  hipLaunchKernelGGL((k_wgrad32<HID>), gw, bw, 0, s, net->act[1], net->dbuf[0], part(2), np, n, h, w, bpw);
   hipLaunchKernelGGL((k_conv<HID, HID>), g, b, 0, s, net->dbuf[0], net->wb[2], net->act[1], net->dbuf[1], n, h,
                      w);
   // layer 2
-  hipLaunchKernelGGL((k_wgrad<HID, HID, HID, HID, HID>), gw, b, 0, s, net->act[0], net->dbuf[1], net->wpart,
-                     n, h, w, bpw);
-  wsum(L[1]);
+  hipLaunchKernelGGL((k_wgrad32<HID>), gw, bw, 0, s, net->act[0], net->dbuf[1], part(1), np, n, h, w, bpw);
   hipLaunchKernelGGL((k_conv<HID, HID>), g, b, 0, s, net->dbuf[1], net->wb[1], net->act[0], net->dbuf[0], n, h,
                      w);
   // layer 1
-  hipLaunchKernelGGL((k_wgrad<4, 3, HID, HID, HID>), gw, b, 0, s, net->xin, net->dbuf[0], net->wpart, n, h, w,
-                     bpw);
-  wsum(L[0]);
-  e = hipGetLastError();
-  if (e == hipSuccess && grads && grads != net->grads)
-    e = hipMemcpyAsync(grads, net->grads, (size_t)net->n_params * 4, hipMemcpyDeviceToDevice, s);
+  hipLaunchKernelGGL(k_wgrad, dim3(rows0), b, 0, s, net->xin, net->dbuf[0], part(0), np, n, h,
+                     w, bpw0);
+  // every layer's rows into the gradient, and into the caller's copy
+  hipLaunchKernelGGL(k_wsum, dim3((np + 63) / 64), dim3(512), 0, s, (const float*)net->wpart, rows0, L[1].w_off,
+                     rows, np, net->grads,
+                     grads == net->grads ? nullptr : grads);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "wv_cnn_backward");
   return WV_OK;
 }
