@@ -63,6 +63,55 @@ std::vector<int> kept_table(int p, int levels) {
   return kept;
 }
 
+// storage_order as (by << 8) | bx, by counting: a block's level depends only on
+// the larger of its two coordinates (sorting took several us per call).
+void storage_order_packed(int p, int levels, uint16_t* out) {
+  const int nbx = p / block_edge(p);
+  int lev[kRebuildMaxBlocks], at[34] = {};
+  for (int m = 0; m < nbx; ++m) {
+    lev[m] = block_level(p, levels, m, 0);
+    at[levels + 1 - lev[m] + 1] += 2 * m + 1;   // blocks whose larger coordinate is m
+  }
+  for (int k = 1; k < 34; ++k) at[k] += at[k - 1];
+  for (int by = 0; by < nbx; ++by)
+    for (int bx = 0; bx < nbx; ++bx) out[at[levels + 1 - lev[std::max(by, bx)]]++] = (uint16_t)((by << 8) | bx);
+}
+
+// The geometry of a frame's planes for the rebuild kernel, and the storage
+// orders of its tiles.
+void rebuild_geometry(const wv_ctx* c, RebuildArgs& a) {
+  memset(&a, 0, sizeof a);
+  a.nplanes = c->nplanes;
+  a.levels = c->d.levels;
+  for (int p = 0; p < a.nplanes; ++p) {
+    RebuildPlane& pl = a.plane[p];
+    pl.p = plane_edge(c->d, p);
+    pl.b = block_edge(pl.p);
+    pl.nb = (pl.p / pl.b) * (pl.p / pl.b);
+    pl.order0 = p ? a.plane[0].nb : 0;
+    a.per_item += pl.nb;
+    if (p < 2) storage_order_packed(pl.p, a.levels, a.order + pl.order0);
+  }
+}
+
+void rebuild_bounds(const float* bounds, RebuildPlane& pl) {
+  for (int k = 0; k < 2; ++k) {
+    const double lo = bounds[2 * k], hi = bounds[2 * k + 1];
+    pl.lo[k] = (float)lo;
+    pl.scale[k] = (float)((hi - lo) / 255.0);
+  }
+}
+
+hipError_t launch_rebuild_items(const wv_ctx* c, RebuildArgs& a, const std::vector<Item>& items, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  for (size_t i0 = 0; e == hipSuccess && i0 < items.size(); i0 += kArgItems) {
+    a.n_items = (int)std::min<size_t>(kArgItems, items.size() - i0);
+    std::copy(items.begin() + i0, items.begin() + i0 + a.n_items, a.items);
+    e = launch_rebuild(c->d.wavelet, a, s);
+  }
+  return e;
+}
+
 bool plane_geometry(const wv_desc* d, int plane, int& p, int& height, int& tiles_x, int& n_tiles) {
   if (!d || d->tile < 8 || d->width % d->tile || d->height % d->tile) return false;
   const int nplanes = d->format == WV_YUV420 ? 3 : 1;
@@ -205,34 +254,21 @@ extern "C" wv_status wv_sparse_rebuild(wv_ctx* c, const wv_sparse_plane* planes,
     it.lc = (uint8_t)l;
     items.push_back(it);
   }
+  if (items.empty()) return WV_OK;
+  RebuildArgs a;
+  rebuild_geometry(c, a);
   for (int p = 0; p < c->nplanes; ++p) {
     const wv_sparse_plane& sp = planes[p];
-    RebuildArgs a;
-    memset(&a, 0, sizeof a);
-    a.block_end = sp.block_end;
-    a.values = sp.values;
-    a.index = sp.index;
-    a.n_records = (uint64_t)sp.n_records;
-    a.dense = dense[p];
-    a.p = plane_edge(c->d, p);
-    a.levels = c->d.levels;
-    a.b = block_edge(a.p);
-    const auto order = storage_order(a.p, a.levels);
-    a.nb = (int)order.size();
-    for (int j = 0; j < a.nb; ++j) a.order[j] = (uint16_t)((order[j].first << 8) | order[j].second);
-    for (int k = 0; k < 2; ++k) {
-      const double lo = sp.bounds[2 * k], hi = sp.bounds[2 * k + 1];
-      a.lo[k] = (float)lo;
-      a.scale[k] = (float)((hi - lo) / 255.0);
-    }
-    for (size_t i0 = 0; i0 < items.size(); i0 += kArgItems) {
-      const int n = (int)std::min<size_t>(kArgItems, items.size() - i0);
-      std::copy(items.begin() + i0, items.begin() + i0 + n, a.items);
-      a.n_items = n;
-      const hipError_t e = launch_rebuild(c->d.wavelet, a, s);
-      if (e != hipSuccess) return hip_fail(e, "rebuild launch");
-    }
+    RebuildPlane& pl = a.plane[p];
+    pl.block_end = sp.block_end;
+    pl.values = sp.values;
+    pl.index = sp.index;
+    pl.n_records = (uint64_t)sp.n_records;
+    pl.dense = dense[p];
+    rebuild_bounds(sp.bounds, pl);
   }
+  const hipError_t e = launch_rebuild_items(c, a, items, s);
+  if (e != hipSuccess) return hip_fail(e, "rebuild launch");
   return WV_OK;
 }
 
@@ -365,7 +401,6 @@ struct wv_prefetch {
   Slot slot[kPrefetchSlots];
   int next_stage = 0, next_rebuild = 0;
   std::vector<int> kept[3];                    // kept_table of each plane
-  std::vector<uint16_t> order[3];              // storage order of each plane
   // the prepare thread
   std::thread worker;
   std::mutex mu;
@@ -520,7 +555,6 @@ extern "C" wv_status wv_prefetch_create(wv_ctx* c, int32_t max_frames, int64_t s
   for (int p = 0; p < c->nplanes; ++p) {
     const int edge = plane_edge(c->d, p);
     pf->kept[p] = kept_table(edge, c->d.levels);
-    for (const auto& b : storage_order(edge, c->d.levels)) pf->order[p].push_back((uint16_t)((b.first << 8) | b.second));
   }
   hipError_t e = hipSetDevice(c->device);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&pf->copy, hipStreamNonBlocking);
@@ -642,33 +676,21 @@ extern "C" wv_status wv_prefetch_rebuild(wv_prefetch* pf, void* const* dense, hi
   }
   hipError_t e = hipSetDevice(c->device);
   if (e == hipSuccess) e = hipStreamWaitEvent(s, pf->copied[k], 0);
-  for (int i = 0; e == hipSuccess && i < nfp; ++i) {
-    const StagedPlane& sp = sl.planes[i];
-    RebuildArgs a;
-    memset(&a, 0, sizeof a);
-    a.block_end = (const uint32_t*)(pf->dev[k] + sp.be_off);
-    a.index = (const uint16_t*)(pf->dev[k] + sp.idx_off);
-    a.values = pf->dev[k] + sp.val_off;
-    a.n_records = (uint64_t)sp.n;
-    a.dense = dense[i];
-    a.compact = 1;
-    a.p = plane_edge(c->d, i % np);
-    a.levels = c->d.levels;
-    a.b = block_edge(a.p);
-    const std::vector<uint16_t>& order = pf->order[i % np];
-    a.nb = (int)order.size();
-    std::copy(order.begin(), order.end(), a.order);
-    for (int q = 0; q < 2; ++q) {
-      const double lo = sp.bounds[2 * q], hi = sp.bounds[2 * q + 1];
-      a.lo[q] = (float)lo;
-      a.scale[q] = (float)((hi - lo) / 255.0);
+  RebuildArgs a;
+  rebuild_geometry(c, a);
+  a.compact = 1;
+  for (int f = 0; e == hipSuccess && f < sl.n_frames; ++f) {   // a frame's planes in one launch
+    for (int p = 0; p < np; ++p) {
+      const StagedPlane& sp = sl.planes[f * np + p];
+      RebuildPlane& pl = a.plane[p];
+      pl.block_end = (const uint32_t*)(pf->dev[k] + sp.be_off);
+      pl.index = (const uint16_t*)(pf->dev[k] + sp.idx_off);
+      pl.values = pf->dev[k] + sp.val_off;
+      pl.n_records = (uint64_t)sp.n;
+      pl.dense = dense[f * np + p];
+      rebuild_bounds(sp.bounds, pl);
     }
-    for (size_t i0 = 0; e == hipSuccess && i0 < sl.items.size(); i0 += kArgItems) {
-      const int n = (int)std::min<size_t>(kArgItems, sl.items.size() - i0);
-      std::copy(sl.items.begin() + i0, sl.items.begin() + i0 + n, a.items);
-      a.n_items = n;
-      e = launch_rebuild(c->d.wavelet, a, s);
-    }
+    e = launch_rebuild_items(c, a, sl.items, s);
   }
   if (e == hipSuccess) e = hipEventRecord(pf->consumed[k], s);
   if (e != hipSuccess) return hip_fail(e, "wv_prefetch_rebuild");

@@ -112,20 +112,24 @@ hipError_t launch_strip97_set(int format, int shape, int L, const WorkArgs& a, h
 hipError_t launch_plain(int wavelet, int format, const PlainArgs& a, hipStream_t s);
 
 // Rebuild of dense planes from the sparse format: one workgroup per (visible
-// tile, block) of one plane.
-constexpr int kRebuildMaxBlocks = 256;   // blocks per tile (512-sample tiles)
-struct RebuildArgs {
+// tile, block) of every plane of a frame.
+constexpr int kRebuildMaxBlocks = 256;   // blocks per luma tile (512-sample tiles)
+struct RebuildPlane {
   const uint32_t* block_end;
   const uint8_t* values;
   const uint16_t* index;
   uint64_t n_records;
   void* dense;                           // [n_tiles][P][P] int16 or float32
-  int32_t p, levels, b, nb;              // tile edge, levels, block edge, blocks per tile
   float lo[2], scale[2];                 // [0] approximation, [1] details
-  int32_t n_items;
+  int32_t p, b, nb, order0;              // tile edge, block edge, blocks per tile, its part of order[]
+};
+struct RebuildArgs {
+  RebuildPlane plane[3];
+  int32_t nplanes, levels, n_items;
+  int32_t per_item;                      // blocks per tile, all planes
   int32_t compact;                       // block_end indexed by item slot (staged
                                          // records of the visible tiles only)
-  uint16_t order[kRebuildMaxBlocks];     // storage order: (by << 8) | bx
+  uint16_t order[kRebuildMaxBlocks * 5 / 4];   // storage order, luma then chroma: (by << 8) | bx
   Item items[kArgItems];
 };
 static_assert(sizeof(RebuildArgs) <= 4000, "kernel arguments must stay under 4 KB");
