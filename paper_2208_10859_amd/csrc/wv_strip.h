@@ -302,6 +302,10 @@ __device__ __forceinline__ void ld_px(const WV_G float* p, float (&v)[N]) {
   }
 }
 
+__device__ __forceinline__ uint16_t pack2(int a, int b) {
+  return (uint16_t)perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);
+}
+
 // Prefetched reference rows of a segment (up to 8 pairs).  8-bit samples stay
 // packed as loaded (a quarter of the registers) and are taken apart where
 // they are added; float samples are kept as they are.
@@ -344,6 +348,14 @@ struct RefRows<uint8_t, C> {
     }
   }
   __device__ __forceinline__ void set(int row, int k, uint32_t v) { w[row][k] = v; }
+  __device__ __forceinline__ void keep(int row, const int (&y)[C]) {
+    if constexpr (C == 2) {
+      w[row][0] = pack2(y[0], y[1]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < W; ++k) w[row][k] = pack4(y[4 * k], y[4 * k + 1], y[4 * k + 2], y[4 * k + 3]);
+    }
+  }
   __device__ __forceinline__ int get(int row, int c) const { return (w[row][c >> 2] >> (8 * (c & 3))) & 0xff; }
 };
 template <int C>
@@ -359,11 +371,12 @@ struct RefRows<float, C> {
   __device__ __forceinline__ void load(int row, const WV_G float* p) { ld_px<C>(p, v[row]); }
   __device__ __forceinline__ void load_lds(int row, const float* p) { ld_lds<C>(p, v[row]); }
   __device__ __forceinline__ float get(int row, int c) const { return v[row][c]; }
+  __device__ __forceinline__ void keep(int row, const float (&y)[C]) {
+#pragma unroll
+    for (int k = 0; k < C; ++k) v[row][k] = y[k];
+  }
 };
 
-__device__ __forceinline__ uint16_t pack2(int a, int b) {
-  return (uint16_t)perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);
-}
 
 // 8-bit colour conversion on pairs of 16-bit halves.  A luma sample y is held
 // as 0xff00 + y; a colour term t (the Q16 JFIF term of one chroma sample,
@@ -409,6 +422,28 @@ __device__ __forceinline__ void st_px(WV_G float* p, const float (&v)[N]) {
     for (int k = 0; k < N; k += 4) *(WV_G f32x4*)(p + k) = f32x4{v[k], v[k + 1], v[k + 2], v[k + 3]};
   } else {
     *(WV_G f32x2*)p = f32x2{v[0], v[1]};
+  }
+}
+
+// The same as a streaming store (output is not read again by the decode).
+template <int N>
+__device__ __forceinline__ void st_px_nt(WV_G uint8_t* p, const int (&v)[N]) {
+  if constexpr (N == 8) {
+    __builtin_nontemporal_store(u32x2{pack4(v[0], v[1], v[2], v[3]), pack4(v[4], v[5], v[6], v[7])}, (WV_G u32x2*)p);
+  } else if constexpr (N == 4) {
+    __builtin_nontemporal_store(pack4(v[0], v[1], v[2], v[3]), (WV_G uint32_t*)p);
+  } else {
+    __builtin_nontemporal_store(pack2(v[0], v[1]), (WV_G uint16_t*)p);
+  }
+}
+template <int N>
+__device__ __forceinline__ void st_px_nt(WV_G float* p, const float (&v)[N]) {
+  if constexpr (N % 4 == 0) {
+#pragma unroll
+    for (int k = 0; k < N; k += 4)
+      __builtin_nontemporal_store(f32x4{v[k], v[k + 1], v[k + 2], v[k + 3]}, (WV_G f32x4*)(p + k));
+  } else {
+    __builtin_nontemporal_store(f32x2{v[0], v[1]}, (WV_G f32x2*)p);
   }
 }
 
@@ -626,8 +661,8 @@ struct LumaOut {
   const RT* chr1;     // Cr
   int j0, r0;
   bool wref;             // store the new reference rows to memory
-  RefRows<RT, C>* refv;  // this wave's reference rows (zero for intra frames); the 5/3
-                         // colour path leaves the new rows in it
+  RefRows<RT, C>* refv;  // this wave's reference rows (zero for intra frames); the new
+                         // rows are left in it
   // n packed words to a plane row; NT: streaming stores (the output is not
   // read again by the decode)
   template <int NWD, bool NT = false>
@@ -698,6 +733,17 @@ struct LumaOut {
       st_words<NWD, true>(at(out + (o + 2 * PL), lo), wb);
     }
   }
+  // Output samples: streaming stores, except for float RGB of 512-sample tiles
+  // with a reference: a lane's eight floats leave as two stores of every other
+  // 16 bytes, and plain stores are the better ones there (a 9/7 frame 60.6
+  // against 62.8 us, a foveated GOP 332 against 357).  Elsewhere, streaming
+  // against plain: 9/7 GOPs of 256-sample tiles 141 / 181, of 128-sample ones
+  // 193 / 234, a 9/7 set of four 228 / 269, grey GOPs 115 / 120 us.
+  static constexpr bool NT = !(sizeof(RT) == 4 && FMT == WV_YUV420 && C == 8 && WREF);
+  __device__ __forceinline__ static void st_out(WV_G RT* p, const V (&v)[C]) {
+    if constexpr (NT) st_px_nt<C>(p, v);
+    else st_px<C>(p, v);
+  }
   template <int J>
   __device__ __forceinline__ void pair(const V (&xe)[C], const V (&xo)[C]) {
     const int r = 2 * (j0 + J);
@@ -712,6 +758,8 @@ struct LumaOut {
       return;
     }
     if constexpr (WREF) {
+      refv->keep(2 * J, y[0]);
+      refv->keep(2 * J + 1, y[1]);
       if (wref) {
         st_px<C>(at(ref + r * N, lo), y[0]);
         st_px<C>(at(ref + (r + 1) * N, lo), y[1]);
@@ -719,8 +767,8 @@ struct LumaOut {
     }
     if (!out) return;
     if constexpr (FMT == WV_GRAY8) {
-      st_px<C>(at(out + r * N, lo), y[0]);
-      st_px<C>(at(out + (r + 1) * N, lo), y[1]);
+      st_out(at(out + r * N, lo), y[0]);
+      st_out(at(out + (r + 1) * N, lo), y[1]);
     } else {
       constexpr int HC = C / 2;
       const int cr = (r >> 1) - (r0 >> 1);   // chroma strip row
@@ -754,9 +802,9 @@ struct LumaOut {
           Bv[c] = clip255(y[h][c] + tb[c >> 1]);
         }
         const unsigned o = (unsigned)((r + h) * N);
-        st_px<C>(at(out + o, lo), R);
-        st_px<C>(at(out + (o + PL), lo), Gv);
-        st_px<C>(at(out + (o + 2 * PL), lo), Bv);
+        st_out(at(out + o, lo), R);
+        st_out(at(out + (o + PL), lo), Gv);
+        st_out(at(out + (o + 2 * PL), lo), Bv);
       }
     }
   }
@@ -911,7 +959,7 @@ __device__ __forceinline__ void push_rows(int t, int& rs, int& rd) {
 }
 
 // The global loads of one segment: for push i, the low-band row (level L
-// only) and the three detail rows, each one vector offset (the lane's column
+// only) and the three detail rows (unless DROP), each one vector offset (the lane's column
 // plus the row) from the plane's scalar base.
 template <class LF, int N, int PP, int K, bool FROM_LL, bool DROP, class SRC, bool SET>
 __device__ __forceinline__ void seg_load(const SRC& coef, int g, int j0,
@@ -1037,26 +1085,9 @@ constexpr int chroma_pairs() {
 // Level l of one plane: the pairs of its cone rows [a, b) in segments of K,
 // dealt to `nwp` waves (this wave is number `rank` among them; with several
 // rows per wave each lane slot takes its own segment).
-// The loads of level l of a plane (one row per wave) for this wave's first
-// segment: issued early by the caller, consumed by `level` (argument pre).
-template <class LF, int PP, int L, int l, int K, class SRC>
-using PreLoads = SegLoads<LF, (PP >> (l - 1)), K, l == L, IsSet<SRC>::value>;
-
-template <class LF, int PP, int L, int l, int K, class SRC>
-__device__ __forceinline__ void level_preload(const Plane<LF, L, SRC>& pl, int lc, int rank, int lane,
-                                              PreLoads<LF, PP, L, l, K, SRC>& ld) {
-  constexpr int N = PP >> (l - 1);
-  static_assert(RL<N>::S == 1, "one row per wave");
-  const int j0 = (pl.a[l] >> 1) + rank * K;
-  if (l <= L - lc)
-    seg_load<LF, N, PP, K, l == L, true>(pl.coef, lane, j0, ld);
-  else
-    seg_load<LF, N, PP, K, l == L, false>(pl.coef, lane, j0, ld);
-}
-
-template <class LF, int PP, int L, int l, int K, class MakeEmit, class SRC, class Pre = std::nullptr_t>
+template <class LF, int PP, int L, int l, int K, class MakeEmit, class SRC>
 __device__ __forceinline__ void level(const Plane<LF, L, SRC>& pl, int qstep, int lc, int rank,
-                                      int nwp, int lane, MakeEmit&& make_emit, const Pre* pre = nullptr) {
+                                      int nwp, int lane, MakeEmit&& make_emit) {
   constexpr int N = PP >> (l - 1);
   using RLN = RL<N>;
   constexpr int S = RLN::S, G = RLN::G;
@@ -1076,15 +1107,6 @@ __device__ __forceinline__ void level(const Plane<LF, L, SRC>& pl, int qstep, in
     const int t = t0 + q;
     const int j0 = (pl.a[l] >> 1) + t * K;
     auto emit = make_emit(g, j0, min(max(np - t * K, 0), K));
-    if constexpr (!std::is_same<Pre, std::nullptr_t>::value) {
-      if (t0 == rank * S) {   // this wave's first segment: its loads are in *pre
-        if (drop)
-          seg_run<LF, N, PP, K, l == L, true>(*pre, qstep, s_win, sa, srows, g, j0, emit);
-        else
-          seg_run<LF, N, PP, K, l == L, false>(*pre, qstep, s_win, sa, srows, g, j0, emit);
-        continue;
-      }
-    }
     if (drop)
       segment<LF, N, PP, K, l == L, true>(pl.coef, qstep, s_win, sa, srows, g, j0, emit);
     else
@@ -1092,16 +1114,16 @@ __device__ __forceinline__ void level(const Plane<LF, L, SRC>& pl, int qstep, in
   }
 }
 
-template <class LF, int PP, int L, int l, int K, class SRC, class Pre = std::nullptr_t>
+template <class LF, int PP, int L, int l, int K, class SRC>
 __device__ __forceinline__ void coarse_level(const Plane<LF, L, SRC>& pl, int qstep, int lc,
-                                             int rank, int nwp, int lane, const Pre* pre = nullptr) {
+                                             int rank, int nwp, int lane) {
   constexpr int N = PP >> (l - 1), C = RL<N>::C;
   using V = typename LF::V;
   V* win = pl.win[l & 1];
   const int a = pl.a[l];
   level<LF, PP, L, l, K>(pl, qstep, lc, rank, nwp, lane, [&](int g, int j0, int kk) {
     return ToWindow<V, N, C>{win + g * C, j0, kk, a};
-  }, pre);
+  });
 }
 
 // Reference rows of a segment's pairs, fetched before the lifting starts.
@@ -1143,6 +1165,18 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+// The coarse levels L .. LAST of a plane as a chain on one wave (strips of ROWS
+// rows).  (Loading the first segments of every level before the first is
+// computed was slower: 8 to 15 % for 9/7 GOPs.)
+template <class LF, int PP, int L, int LAST, int ROWS, class SRC>
+__device__ __forceinline__ void chain(const Plane<LF, L, SRC>& pl, int qstep, int lc, int lane) {
+  static_for_down<L, LAST - 1>([&](auto LL) {
+    constexpr int l = decltype(LL)::value;
+    coarse_level<LF, PP, L, l, seg_pairs<LF, (PP >> (l - 1)), ROWS, l, 1>()>(pl, qstep, lc, 0, 1, lane);
+    wave_lds_sync();
+  });
+}
+
 // SCHED 0: phase k computes luma level L+1-k and chroma level L-k on all
 // waves, one barrier per phase.  SCHED 1: each plane's coarse levels run as a
 // chain on one wave (luma L..3 on wave 0, chroma L..2 on waves 1 and 2) with
@@ -1163,8 +1197,12 @@ __device__ __forceinline__ std::conditional_t<SET, SetSrc<CT>, const WV_G CT*> p
 
 // first / last: the unit's first and last frame in this launch.  In the GOP
 // form a strip's reference rows stay on chip between its frames (luma in the
-// waves' registers `lkeep` for 8-bit samples, chroma in the strip's LDS rows)
-// and reach memory only after the last frame.
+// waves' registers `lkeep`, chroma in the strip's LDS rows) and reach memory
+// only after the last frame.  Float luma of 512-sample tiles takes 32 registers
+// for it, still three waves per SIMD (138 -> 152): an 8-frame foveated 9/7 GOP
+// of 8192 x 8192 404 -> 332 us.  Float luma of 128-sample tiles goes through
+// memory: their reference stays in the cache, and the registers cost a wave
+// per SIMD (234 against 224 us).
 template <class LF, int FMT, int P, int L, int R, int NW, int SCHED, bool SET>
 __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, const WorkArgs& a, int unit,
                                            int frame, bool first, bool last,
@@ -1184,7 +1222,7 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
   // inter-frame-set frames stand alone: no reference is read or written
   const bool intra = SET || (job.flags & kJobIntra) != 0;
   const bool has_out = (job.flags & kJobHasOut) != 0;
-  constexpr bool KEEPY = sizeof(RT) == 1 && YUV && !SET && RL<P>::C % 4 == 0, KEEPC = YUV && !SET;
+  constexpr bool KEEPY = !SET && (sizeof(RT) == 1 || P >= 256), KEEPC = YUV && !SET;
   const bool wref_y = !KEEPY || last, wref_c = !KEEPC || last;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   int lane = threadIdx.x & 63;
@@ -1197,15 +1235,22 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
   py.win[0] = sm.ya();
   py.win[1] = sm.yb;
   cone<LF, L>(st * R, R, P, py.a, py.b);
-  Plane<LF, L, SrcT> pc[2];
+  // Phased schedule: both chroma planes, each with code of its own (a phase's
+  // waves may take either).  Chain schedule: waves 1 and 2 take one plane each
+  // through the same code; with a copy per plane the 9/7 kernel was 91 KB, more
+  // than the instruction cache holds; shared 64 KB (GOPs 1 to 2 % faster).
+  constexpr int NPC = SCHED == 1 ? 1 : 2;
+  const int cp = SCHED == 1 ? (wave == 2) : 0;   // the plane of pc[0]
+  Plane<LF, L, SrcT> pc[NPC];
   if constexpr (YUV) {
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      pc[p].coef = plane_src<CT, SET>(job, 1 + p, (size_t)item.tile * PC * PC, job.hstride / 4);
-      pc[p].ref = uniform((WV_G RT*)job.ref[1 + p] + (size_t)item.tile * PC * PC);
-      pc[p].win[0] = sm.ca[p];
-      pc[p].win[1] = sm.cb(p);
-      cone<LF, L>(st * RC, RC, PC, pc[p].a, pc[p].b);
+    for (int k = 0; k < NPC; ++k) {
+      const int p = cp + k;
+      pc[k].coef = plane_src<CT, SET>(job, 1 + p, (size_t)item.tile * PC * PC, job.hstride / 4);
+      pc[k].ref = uniform((WV_G RT*)job.ref[1 + p] + (size_t)item.tile * PC * PC);
+      pc[k].win[0] = sm.ca[p];
+      pc[k].win[1] = sm.cb(p);
+      cone<LF, L>(st * RC, RC, PC, pc[k].a, pc[k].b);
     }
   }
 
@@ -1258,13 +1303,12 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
       else
         seg_run<LF, P, P, K1, L == 1, false>(ly, qs, sw, sa, srows, lane, j0y, lout);
     };
-    // the finest rows of chroma plane pi
-    auto chroma1 = [&](auto PI, int rank, int nwp) __attribute__((always_inline)) {
-      constexpr int pi = decltype(PI)::value;
+    // the finest rows of this wave's chroma plane
+    auto chroma1 = [&]() __attribute__((always_inline)) {
       constexpr int KC = chroma_pairs<PC, RC>(), C = RL<PC>::C;
-      const Plane<LF, L, SrcT>& pl = pc[pi];
-      RT* chr = sm.chr[pi];
-      level<LF, PC, L, 1, KC>(pl, qs, lc, rank, nwp, lane, [&](int g, int j0, int) {
+      const Plane<LF, L, SrcT>& pl = pc[0];
+      RT* chr = sm.chr[YUV ? cp : 0];
+      level<LF, PC, L, 1, KC>(pl, qs, lc, 0, 1, lane, [&](int g, int j0, int) {
         ChromaOut<LF, PC, C, !SET> e;
         e.ref = pl.ref;
         e.lo = (unsigned)(g * C);
@@ -1288,33 +1332,18 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
     constexpr bool phase_a = L >= 3 || (YUV && L >= 2);
     if constexpr (EARLY) luma1_load();
     __builtin_amdgcn_s_setprio(3);
+    const bool cwave = YUV && (wave == 1 || wave == 2);
     if constexpr (L >= 3) {
-      if (wave == 0) {
-        static_for_down<L, 2>([&](auto LL) {
-          constexpr int l = decltype(LL)::value;
-          coarse_level<LF, P, L, l, seg_pairs<LF, (P >> (l - 1)), R, l, 1>()>(py, qs, lc, 0, 1, lane);
-          wave_lds_sync();
-        });
-      }
+      if (wave == 0) chain<LF, P, L, 3, R>(py, qs, lc, lane);
     }
     if constexpr (YUV && L >= 2) {
-      static_for<0, 2>([&](auto PI) {
-        constexpr int pi = decltype(PI)::value;
-        if (wave == 1 + pi) {
-          static_for_down<L, 1>([&](auto LL) {
-            constexpr int l = decltype(LL)::value;
-            coarse_level<LF, PC, L, l, seg_pairs<LF, (PC >> (l - 1)), RC, l, 1>()>(pc[pi], qs, lc, 0, 1, lane);
-            wave_lds_sync();
-          });
-        }
-      });
+      if (cwave) chain<LF, PC, L, 2, RC>(pc[0], qs, lc, lane);
     }
     if constexpr (phase_a) lds_barrier();
     __builtin_amdgcn_s_setprio(1);
     // B: luma level 2 on the waves not busy with chroma, the finest chroma
     // rows on waves 1 and 2
     if constexpr (L >= 2 || YUV) {
-      const bool cwave = YUV && (wave == 1 || wave == 2);
       if constexpr (L >= 2) {
         if (!cwave) {
           const int rank = YUV ? (wave == 0 ? 0 : wave - 2) : wave, nwp = YUV ? NW - 2 : NW;
@@ -1322,9 +1351,7 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
         }
       }
       if constexpr (YUV) {
-        static_for<0, 2>([&](auto PI) {
-          if (wave == 1 + decltype(PI)::value) chroma1(PI, 0, 1);
-        });
+        if (cwave) chroma1();
       }
       lds_barrier();
     }
