@@ -10,7 +10,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <vector>
 
 #include "wv_cnn.h"
 #include "wv_ctx.h"
@@ -564,18 +563,19 @@ void k_wgrad32(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, 
 // and writes the gradient (and the caller's copy) in a fixed order.
 // What bounds it: the rows' bytes.  One launch per
 // layer with atomics into a cleared gradient, and a copy of it, took
-// 4 x 4.5 + 8 us of a 16 x 128 x 128 step; this one takes 7 us (26 MB).
-// rows0: rows of the parameters below `first` (the first layer's), rows: of the
-// others.
-__global__ __launch_bounds__(512) void k_wsum(const float* __restrict__ part, int rows0, int first, int rows,
-                                              int width, float* __restrict__ g, float* __restrict__ g2) {
+// 4 x 4.5 + 8 us of a 16 x 128 x 128 step; this one takes 7 us (22 MB).
+// part: rows0 rows of the `first` parameters of the first layer, then (from
+// `rest` on) `rows` rows of the others.
+__global__ __launch_bounds__(512) void k_wsum(const float* __restrict__ part, int rows0, int first,
+                                              const float* __restrict__ rest, int rows, int width, float* __restrict__ g, float* __restrict__ g2) {
   __shared__ float red[8][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.x * 64 + lane;
   float s = 0.f;
   if (j < width) {
-    const int n = j < first ? rows0 : rows;
+    const int n = j < first ? rows0 : rows, stride = j < first ? first : width - first;
+    const float* p = j < first ? part + j : rest + (j - first);
 #pragma unroll 8
-    for (int r = wave; r < n; r += 8) s += part[(size_t)r * width + j];
+    for (int r = wave; r < n; r += 8) s += p[(size_t)r * stride];
   }
   red[wave][lane] = s;
   __syncthreads();
@@ -950,81 +950,129 @@ __global__ void k_gather(const uint8_t* __restrict__ img, int T, int tx, int ty,
   }
 }
 
-// A whole tile-planar viewport (ty x tx tiles of T x T) as one bfloat16
-// NHWC4 image in [0, 1].
-__global__ void k_to_nhwc(const uint8_t* __restrict__ img, int T, int tx, int ty,
-                          uint16_t* __restrict__ out) {
+// Restoration of a viewport around the forward pass: three kernels that move
+// bytes, V pixels of a row per thread (4 where the tile edge allows it).  The
+// guard decides on the device, so that the host waits once, at the end.
+// 2048 x 2048 (us): to_nhwc 15.9 -> 10.8, guard 20.6 -> 11.4 + 4.8, restore
+// 21.6 -> 14.6; the whole call, in which the host used to decide between guard
+// and restore: 337 -> 299.
+template <int V>
+struct __attribute__((packed, aligned(1))) Bytes { uint8_t v[V]; };
+
+// The whole tile-planar viewport (ty x tx tiles of T x T) as one bfloat16
+// NHWC4 image in [0, 1]; clears the count of fallback tiles.
+template <int V>
+__global__ __launch_bounds__(256) void k_to_nhwc(const uint8_t* __restrict__ img, int T, int tx, int ty,
+                                                 uint2* __restrict__ out, int* __restrict__ fell) {
   const int W = T * tx;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  const int p = (blockIdx.x * 256 + threadIdx.x) * V;
+  if (p == 0) *fell = 0;
   if (p >= W * T * ty) return;
   const int y = p / W, xg = p % W;
-  const size_t base = ((size_t)(y / T) * tx + xg / T) * 3 * T * T + (size_t)(y % T) * T + xg % T;
+  const uint8_t* src = img + ((size_t)(y / T) * tx + xg / T) * 3 * T * T + (size_t)(y % T) * T + xg % T;
+  Bytes<V> c[3];
 #pragma unroll
-  for (int c = 0; c < 4; ++c)
-    out[(size_t)p * 4 + c] = c < 3 ? f2bf(img[base + (size_t)c * T * T] * (1.f / 255.f)) : (uint16_t)0;
+  for (int k = 0; k < 3; ++k) c[k] = *(const Bytes<V>*)(src + (size_t)k * T * T);
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    uint32_t h[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) h[k] = f2bf(c[k].v[v] * (1.f / 255.f));
+    out[p + v] = make_uint2(h[0] | (h[1] << 16), h[2]);
+  }
 }
 
-// Per-tile guard statistics of a restored viewport: sum of |z| and a count
-// of non-finite values, per T x T tile.  One workgroup per (tile, band of
-// `rows` rows) sums its pixels and adds once per tile: per-pixel atomics on
-// one address per tile serialise in the cache and took milliseconds.
-__global__ __launch_bounds__(256) void k_guard(const float* __restrict__ z, int T, int tx, int rows,
-                                               float* __restrict__ absz, int* __restrict__ bad) {
-  const int W = T * tx;
-  const int tile = blockIdx.x, tyi = tile / tx, txi = tile - tyi * tx;
-  const int r0 = blockIdx.y * rows, r1 = min(r0 + rows, T);
-  float s = 0.f;
-  int nb = 0;
-  for (int i = threadIdx.x; i < (r1 - r0) * T; i += 256) {
-    const int r = r0 + i / T, c = i - (i / T) * T;
-    const size_t p = (size_t)(tyi * T + r) * W + txi * T + c;
-#pragma unroll
-    for (int ch = 0; ch < 3; ++ch) {
-      const float v = z[p * 4 + ch];
-      if (!isfinite(v)) ++nb;
-      else s += fabsf(v);
-    }
-  }
+// The guard of a restored viewport: per T x T tile the sum of |z| and the
+// number of non-finite values.  One workgroup per (tile, band of `rows` rows)
+// leaves its sums in part[]; k_guard_decide adds a tile's bands in order.  (The
+// last workgroup of a tile deciding instead, behind an agent-scope release,
+// took 41 us: every workgroup then writes its caches back.)
+struct GuardPart { float s; int bad; };
+__device__ __forceinline__ void wave_sum(float& s, int& nb) {
 #pragma unroll
   for (int m = 1; m < 64; m <<= 1) {
     s += __shfl_xor(s, m);
     nb += __shfl_xor(nb, m);
   }
+}
+__global__ __launch_bounds__(256) void k_guard(const float4* __restrict__ z, int T, int tx, int rows,
+                                               GuardPart* __restrict__ part) {
+  const int W = T * tx;
+  const int tile = blockIdx.x, tyi = tile / tx, txi = tile - tyi * tx;
+  const int r0 = blockIdx.y * rows, r1 = min(r0 + rows, T);
+  float s = 0.f;
+  int nb = 0;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < (r1 - r0) * T; i += 256) {
+    const int r = r0 + i / T, c = i - (i / T) * T;
+    const float4 v4 = z[(size_t)(tyi * T + r) * W + txi * T + c];
+    const float v[3] = {v4.x, v4.y, v4.z};
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) {
+      if (!isfinite(v[ch])) ++nb;
+      else s += fabsf(v[ch]);
+    }
+  }
+  wave_sum(s, nb);
   __shared__ float rs[4];
   __shared__ int rn[4];
-  const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
-    rs[wave] = s;
-    rn[wave] = nb;
+    rs[threadIdx.x >> 6] = s;
+    rn[threadIdx.x >> 6] = nb;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    atomicAdd(&absz[tile], rs[0] + rs[1] + rs[2] + rs[3]);
-    const int n = rn[0] + rn[1] + rn[2] + rn[3];
-    if (n) atomicAdd(&bad[tile], n);
+  if (threadIdx.x == 0)
+    part[(size_t)tile * gridDim.y + blockIdx.y] = {rs[0] + rs[1] + rs[2] + rs[3], rn[0] + rn[1] + rn[2] + rn[3]};
+}
+
+// One wave per tile: use[tile] = 1 if the tile keeps the network's output, that
+// is if every value is finite and the mean correction (0..1 scale) stays
+// within the guard; *fell counts the others.
+__global__ __launch_bounds__(64) void k_guard_decide(const GuardPart* __restrict__ part, int bands, double per_tile,
+                                                     float guard, int* __restrict__ use, int* __restrict__ fell) {
+  const int tile = blockIdx.x;
+  float s = 0.f;
+  int nb = 0;
+  for (int i = threadIdx.x; i < bands; i += 64) {
+    const GuardPart g = part[(size_t)tile * bands + i];
+    s += g.s;
+    nb += g.bad;
   }
+  wave_sum(s, nb);
+  if (threadIdx.x) return;
+  const int ok = nb == 0 && (double)s / per_tile <= (double)guard;
+  use[tile] = ok;
+  if (!ok) atomicAdd(fell, 1);
 }
 
 // Restored viewport: clip(x + z) in 8 bits, or the decoded tile where the
 // guard tripped.
-__global__ void k_restore(const uint8_t* __restrict__ dec, const float* __restrict__ z, int T, int tx,
-                          int ty, const int* __restrict__ use, uint8_t* __restrict__ out) {
+template <int V>
+__global__ __launch_bounds__(256) void k_restore(const uint8_t* dec, const float4* __restrict__ z, int T, int tx, int ty,
+                                                 const int* __restrict__ use, uint8_t* out) {
   const int W = T * tx;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  const int p = (blockIdx.x * 256 + threadIdx.x) * V;
   if (p >= W * T * ty) return;
   const int y = p / W, xg = p % W;
   const int tile = (y / T) * tx + xg / T;
   const size_t base = (size_t)tile * 3 * T * T + (size_t)(y % T) * T + xg % T;
+  Bytes<V> c[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    const uint8_t d = dec[base + (size_t)c * T * T];
-    uint8_t o = d;
-    if (use[tile]) {
-      const float f = d * (1.f / 255.f) + z[(size_t)p * 4 + c];
-      o = (uint8_t)fminf(fmaxf(rintf(f * 255.f), 0.f), 255.f);
+  for (int k = 0; k < 3; ++k) c[k] = *(const Bytes<V>*)(dec + base + (size_t)k * T * T);
+  if (use[tile]) {
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const float4 z4 = z[p + v];
+      const float zc[3] = {z4.x, z4.y, z4.z};
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const float f = c[k].v[v] * (1.f / 255.f) + zc[k];
+        c[k].v[v] = (uint8_t)fminf(fmaxf(rintf(f * 255.f), 0.f), 255.f);
+      }
     }
-    out[base + (size_t)c * T * T] = o;
   }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) *(Bytes<V>*)(out + base + (size_t)k * T * T) = c[k];
 }
 
 }  // namespace cnn
@@ -1038,6 +1086,8 @@ using wvp::hip_fail;
 // weight gradients: at most this many workgroups (the first layer's kernel runs
 // two per CU, the others' one), each writing one row of partial sums
 constexpr int kWgradRows0 = 512, kWgradRows = 256;
+
+constexpr int kMaxGuardTiles = 65536;
 
 struct wv_cnn {
   Layer layer[kLayers];
@@ -1058,11 +1108,10 @@ struct wv_cnn {
   uint16_t* dz = nullptr;       // [P][4]
   float* loss_part = nullptr;   // loss sums, one per workgroup
   uint32_t* loss_done = nullptr;  // workgroups finished (0 between launches)
-  float* guard_abs = nullptr;   // per-tile guard sums
-  int* guard_bad = nullptr;
-  int* guard_use = nullptr;
+  GuardPart* guard_part = nullptr;  // guard sums, one per workgroup
+  int* guard_use = nullptr;         // per tile: keep the network's output; then the count of the others
   int* crops = nullptr;
-  float* wpart = nullptr;       // weight-gradient partial sums, [kWgradRows0][n_params]
+  float* wpart = nullptr;       // weight-gradient partial sums: the first layer's rows, then the others'
   int n = 0, h = 0, w = 0;      // shape of the last forward
   bool fwd_valid = false, grad_valid = false;
   bool prepped = false;
@@ -1095,8 +1144,8 @@ extern "C" wv_status wv_cnn_destroy(wv_cnn* net) {
   if (!net) return WV_OK;
   (void)hipDeviceSynchronize();
   void* ptrs[] = {net->params, net->grads, net->adam_m, net->adam_v, net->x, net->act[0], net->act[1],
-                  net->act[2], net->dbuf[0], net->dbuf[1], net->z, net->dz, net->loss_part, net->loss_done, net->guard_abs,
-                  net->guard_bad, net->guard_use, net->crops, net->wpart};
+                  net->act[2], net->dbuf[0], net->dbuf[1], net->z, net->dz, net->loss_part, net->loss_done, net->guard_part,
+                  net->guard_use, net->crops, net->wpart};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int i = 0; i < kLayers; ++i) {
@@ -1136,12 +1185,16 @@ extern "C" wv_status wv_cnn_create(wv_cnn** out, int64_t max_pixels) {
   alloc((void**)&net->dz, P * 4 * 2);
   alloc((void**)&net->loss_part, kLossGroups * sizeof(float));
   alloc((void**)&net->loss_done, sizeof(uint32_t));
-  alloc((void**)&net->guard_abs, 65536 * sizeof(float));
-  alloc((void**)&net->guard_bad, 65536 * sizeof(int));
-  alloc((void**)&net->guard_use, 65536 * sizeof(int));
+  // a guard workgroup has at least 2048 pixels, or is a tile's only or last one
+  alloc((void**)&net->guard_part, (P / 2048 + kMaxGuardTiles) * sizeof(GuardPart));
+  alloc((void**)&net->guard_use, (kMaxGuardTiles + 1) * sizeof(int));
   alloc((void**)&net->crops, 3 * 4096 * sizeof(int));
-  // a weight-gradient workgroup has at least one pixel
-  alloc((void**)&net->wpart, (size_t)std::min<int64_t>(kWgradRows0, max_pixels) * np);
+  // a weight-gradient workgroup has at least one pixel; every row is written
+  // before it is read
+  const size_t np0 = net->layer[1].w_off, npr = net->n_params - np0;
+  if (e == hipSuccess)
+    e = hipMalloc((void**)&net->wpart, (std::min<size_t>(kWgradRows0, P) * np0 + std::min<size_t>(kWgradRows, P) * npr) *
+                                           sizeof(float));
   if (e != hipSuccess) {
     wv_cnn_destroy(net);
     return e == hipErrorOutOfMemory ? fail(WV_ENOMEM, "wv_cnn buffers: %s", hipGetErrorString(e))
@@ -1268,25 +1321,26 @@ extern "C" wv_status wv_cnn_backward(wv_cnn* net, float* grads, hipStream_t s) {
   const int bpw0 = (nb0 + kWgradRows0 - 1) / kWgradRows0, bpw = (nb + kWgradRows - 1) / kWgradRows;
   const int rows0 = (nb0 + bpw0 - 1) / bpw0, rows = (nb + bpw - 1) / bpw;
   const dim3 gw(rows), bw(64 * GWAVES);
-  auto part = [&](int l) { return net->wpart + L[l].w_off; };
-  const int np = net->n_params;
+  const int np = net->n_params, np0 = L[1].w_off, npr = np - np0;   // parameters of the first layer, of the others
+  float* rest = net->wpart + (size_t)rows0 * np0;
+  auto part = [&](int l) { return rest + (L[l].w_off - np0); };
   // layer 4: dW4 from a3 and dz; d3 = (W4' * dz) masked by a3 > 0
-  hipLaunchKernelGGL((k_wgrad32<4>), gw, bw, 0, s, net->act[2], net->dz, part(3), np, n, h, w, bpw);
+  hipLaunchKernelGGL((k_wgrad32<4>), gw, bw, 0, s, net->act[2], net->dz, part(3), npr, n, h, w, bpw);
   hipLaunchKernelGGL((k_conv<4, HID>), g, b, 0, s, net->dz, net->wb[3], net->act[2], net->dbuf[0], n, h, w);
   // layer 3
-  hipLaunchKernelGGL((k_wgrad32<HID>), gw, bw, 0, s, net->act[1], net->dbuf[0], part(2), np, n, h, w, bpw);
+  hipLaunchKernelGGL((k_wgrad32<HID>), gw, bw, 0, s, net->act[1], net->dbuf[0], part(2), npr, n, h, w, bpw);
   hipLaunchKernelGGL((k_conv<HID, HID>), g, b, 0, s, net->dbuf[0], net->wb[2], net->act[1], net->dbuf[1], n, h,
                      w);
   // layer 2
-  hipLaunchKernelGGL((k_wgrad32<HID>), gw, bw, 0, s, net->act[0], net->dbuf[1], part(1), np, n, h, w, bpw);
+  hipLaunchKernelGGL((k_wgrad32<HID>), gw, bw, 0, s, net->act[0], net->dbuf[1], part(1), npr, n, h, w, bpw);
   hipLaunchKernelGGL((k_conv<HID, HID>), g, b, 0, s, net->dbuf[1], net->wb[1], net->act[0], net->dbuf[0], n, h,
                      w);
   // layer 1
-  hipLaunchKernelGGL(k_wgrad, dim3(rows0), b, 0, s, net->xin, net->dbuf[0], part(0), np, n, h,
-                     w, bpw0);
+  hipLaunchKernelGGL(k_wgrad, dim3(rows0), b, 0, s, net->xin, net->dbuf[0], net->wpart, np0, n,
+                     h, w, bpw0);
   // every layer's rows into the gradient, and into the caller's copy
-  hipLaunchKernelGGL(k_wsum, dim3((np + 63) / 64), dim3(512), 0, s, (const float*)net->wpart, rows0, L[1].w_off,
-                     rows, np, net->grads,
+  hipLaunchKernelGGL(k_wsum, dim3((np + 63) / 64), dim3(512), 0, s, (const float*)net->wpart, rows0, np0,
+                     (const float*)rest, rows, np, net->grads,
                      grads == net->grads ? nullptr : grads);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "wv_cnn_backward");
@@ -1346,45 +1400,36 @@ extern "C" wv_status wv_cnn_restore(wv_cnn* net, const uint8_t* decoded, int32_t
   if (!net || !decoded || !out || tile < 1 || tiles_x < 1 || tiles_y < 1 || !(guard > 0))
     return fail(WV_EINVAL, "wv_cnn_restore: bad argument");
   const int nt = tiles_x * tiles_y;
-  if (nt > 65536) return fail(WV_EINVAL, "wv_cnn_restore: at most 65536 tiles");
+  if (nt > kMaxGuardTiles) return fail(WV_EINVAL, "wv_cnn_restore: at most 65536 tiles");
   const int H = tile * tiles_y, W = tile * tiles_x;
   if ((int64_t)H * W > net->max_pixels) return fail(WV_EINVAL, "wv_cnn_restore: image above max_pixels");
-  const int P = H * W, gb = (P + 255) / 256;
+  const int P = H * W, V = tile % 4 == 0 ? 4 : 1, gb = (P / V + 255) / 256;
+  int* count = net->guard_use + kMaxGuardTiles;
   // the input goes straight into the network's input buffer
-  hipLaunchKernelGGL(k_to_nhwc, dim3(gb), dim3(256), 0, s, decoded, tile, tiles_x, tiles_y, net->x);
+  if (V == 4)
+    hipLaunchKernelGGL(k_to_nhwc<4>, dim3(gb), dim3(256), 0, s, decoded, tile, tiles_x, tiles_y, (uint2*)net->x, count);
+  else
+    hipLaunchKernelGGL(k_to_nhwc<1>, dim3(gb), dim3(256), 0, s, decoded, tile, tiles_x, tiles_y, (uint2*)net->x, count);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "wv_cnn_restore");
   // inference only: the activations are not needed
   wv_status st = forward(net, net->x, 1, H, W, nullptr, false, s);
   if (st != WV_OK) return st;
-  e = hipMemsetAsync(net->guard_abs, 0, nt * sizeof(float), s);
-  if (e == hipSuccess) e = hipMemsetAsync(net->guard_bad, 0, nt * sizeof(int), s);
-  if (e == hipSuccess) {
-    const int rows = std::max(1, 4096 / tile);
-    hipLaunchKernelGGL(k_guard, dim3(nt, (tile + rows - 1) / rows), dim3(256), 0, s, net->z, tile, tiles_x, rows,
-                       net->guard_abs, net->guard_bad);
-    e = hipGetLastError();
-  }
-  std::vector<float> absz(nt);
-  std::vector<int> bad(nt), use(nt);
-  if (e == hipSuccess) e = hipMemcpyAsync(absz.data(), net->guard_abs, nt * sizeof(float), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(bad.data(), net->guard_bad, nt * sizeof(int), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return hip_fail(e, "wv_cnn_restore guard");
-  // guard: a tile keeps the network's output only if every value is finite
-  // and its mean correction (0..1 scale) stays below `guard`
-  int fell = 0;
-  const double per_tile = 3.0 * tile * tile;
-  for (int i = 0; i < nt; ++i) {
-    use[i] = bad[i] == 0 && absz[i] / per_tile <= guard;
-    fell += !use[i];
-  }
-  e = hipMemcpyAsync(net->guard_use, use.data(), nt * sizeof(int), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_restore, dim3(gb), dim3(256), 0, s, decoded, net->z, tile, tiles_x, tiles_y,
+  const int rows = std::max(1, 4096 / tile);
+  const int bands = (tile + rows - 1) / rows;
+  hipLaunchKernelGGL(k_guard, dim3(nt, bands), dim3(256), 0, s, (const float4*)net->z, tile, tiles_x, rows,
+                     net->guard_part);
+  hipLaunchKernelGGL(k_guard_decide, dim3(nt), dim3(64), 0, s, (const GuardPart*)net->guard_part, bands,
+                     3.0 * tile * tile, guard, net->guard_use, count);
+  if (V == 4)
+    hipLaunchKernelGGL(k_restore<4>, dim3(gb), dim3(256), 0, s, decoded, (const float4*)net->z, tile, tiles_x, tiles_y,
                        (const int*)net->guard_use, out);
-    e = hipGetLastError();
-  }
+  else
+    hipLaunchKernelGGL(k_restore<1>, dim3(gb), dim3(256), 0, s, decoded, (const float4*)net->z, tile, tiles_x, tiles_y,
+                       (const int*)net->guard_use, out);
+  e = hipGetLastError();
+  int fell = 0;
+  if (e == hipSuccess) e = hipMemcpyAsync(&fell, count, sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "wv_cnn_restore");
   if (fallback_tiles) *fallback_tiles = fell;
