@@ -110,6 +110,7 @@ wv_status wv_create(wv_ctx** out, const wv_desc* desc) {
     return st;
   }
   c->variant = default_variant(c->d);
+  c->few_variant = few_tiles_variant(c->d);
   if (c->variant < 0) {
     wv_destroy(c);
     return fail(WV_EUNSUPPORTED, "no fused variant fits tile %d", desc->tile);
@@ -166,6 +167,7 @@ wv_status wv_set_variant(wv_ctx* c, int32_t v) {
   if (!var) return fail(WV_EINVAL, "variant %d out of range", v);
   if (!variant_fits(c->d, var)) return fail(WV_EUNSUPPORTED, "variant %s does not fit tile %d", var->name, c->d.tile);
   c->variant = v;
+  c->few_variant = -1;   // the caller's choice holds for every call
   return WV_OK;
 }
 
@@ -248,10 +250,15 @@ void wvp::fill_geometry(const wv_ctx* c, const Variant* var, WorkArgs& a) {
   a.items_dev = nullptr;
 }
 
+// The variant of a call of n visible tiles.
+static int call_variant(const wv_ctx* c, size_t n) {
+  return c->few_variant >= 0 && n <= (size_t)kFewTiles ? c->few_variant : c->variant;
+}
+
 // Launch a job list through kernel arguments, in chunks of kArgItems items.
-static wv_status launch_arg_chunks(const wv_ctx* c, const Job* jobs, int n_jobs,
+static wv_status launch_arg_chunks(const wv_ctx* c, int variant, const Job* jobs, int n_jobs,
                                    const std::vector<Item>& items, hipStream_t s) {
-  const Variant* var = fused_variant(c->d.wavelet, c->d.format, c->variant);
+  const Variant* var = fused_variant(c->d.wavelet, c->d.format, variant);
   WorkArgs a;
   memset(&a, 0, sizeof a);
   fill_geometry(c, var, a);
@@ -262,7 +269,7 @@ static wv_status launch_arg_chunks(const wv_ctx* c, const Job* jobs, int n_jobs,
     std::copy(items.begin() + i0, items.begin() + i0 + n, a.items);
     a.n_items = n;
     a.total = n * bpt;
-    hipError_t e = launch_fused(c->d.wavelet, c->d.format, c->variant, a, c->n_cu, s);
+    hipError_t e = launch_fused(c->d.wavelet, c->d.format, variant, a, c->n_cu, s);
     if (e != hipSuccess) return hip_fail(e, "fused launch");
   }
   return WV_OK;
@@ -305,7 +312,7 @@ extern "C" wv_status wv_decode_viewport(wv_ctx* c, const wv_frame* f, const uint
   if (c->path == WV_PATH_PLAIN)
     st = launch_plain_items(c, job, plan.items, s);
   else
-    st = launch_arg_chunks(c, &job, 1, plan.items, s);
+    st = launch_arg_chunks(c, call_variant(c, plan.items.size()), &job, 1, plan.items, s);
   if (st != WV_OK) return st;
   for (const Item& it : plan.items) ref->tile_stamp[it.tile] = f->frame_index;
   return WV_OK;
@@ -338,7 +345,8 @@ extern "C" wv_status wv_decode_gop(wv_ctx* c, int32_t n_frames, const wv_frame* 
     jobs[f] = make_job(c, &frames[f], ref, out);
   }
   if (plan.items.empty()) return WV_OK;
-  const Variant* var = fused_variant(c->d.wavelet, c->d.format, c->variant);
+  const int variant = call_variant(c, plan.items.size());
+  const Variant* var = fused_variant(c->d.wavelet, c->d.format, variant);
   wv_status st = WV_OK;
   if (c->path == WV_PATH_FUSED && var->kind >= 2) {
     // one launch per group of up to kArgJobs frames: each unit takes its tile
@@ -356,7 +364,7 @@ extern "C" wv_status wv_decode_gop(wv_ctx* c, int32_t n_frames, const wv_frame* 
         std::copy(plan.items.begin() + i0, plan.items.begin() + i0 + n, a.items);
         a.n_items = n;
         a.total = n * bpt;
-        const hipError_t e = launch_fused(c->d.wavelet, c->d.format, c->variant, a, c->n_cu, s);
+        const hipError_t e = launch_fused(c->d.wavelet, c->d.format, variant, a, c->n_cu, s);
         if (e != hipSuccess) {
           st = hip_fail(e, "fused GOP launch");
           break;
@@ -367,7 +375,7 @@ extern "C" wv_status wv_decode_gop(wv_ctx* c, int32_t n_frames, const wv_frame* 
     // other forms: one decode per frame
     for (int f = 0; f < n_frames && st == WV_OK; ++f)
       st = c->path == WV_PATH_PLAIN ? launch_plain_items(c, jobs[f], plan.items, s)
-                                    : launch_arg_chunks(c, &jobs[f], 1, plan.items, s);
+                                    : launch_arg_chunks(c, variant, &jobs[f], 1, plan.items, s);
   }
   if (st != WV_OK) return st;
   for (const Item& it : plan.items) ref->tile_stamp[it.tile] = frames[n_frames - 1].frame_index;
@@ -495,9 +503,10 @@ extern "C" wv_status wv_decode_batch(int32_t n_jobs, const wv_job* jobs, hipStre
   }
   if ((int)items.size() > kTableItems) return fail(WV_EINVAL, "at most %d visible tiles per batch", kTableItems);
   if (!items.empty()) {
-    const Variant* var = fused_variant(c0->d.wavelet, c0->d.format, c0->variant);
+    const int variant = call_variant(c0, items.size());
+    const Variant* var = fused_variant(c0->d.wavelet, c0->d.format, variant);
     if (n_jobs <= kArgJobs && (int)items.size() <= kArgItems) {
-      wv_status st = launch_arg_chunks(c0, table.data(), n_jobs, items, s);
+      wv_status st = launch_arg_chunks(c0, variant, table.data(), n_jobs, items, s);
       if (st != WV_OK) return st;
     } else {
       // device table: stage in pinned memory, copy, launch once
@@ -519,7 +528,7 @@ extern "C" wv_status wv_decode_batch(int32_t n_jobs, const wv_job* jobs, hipStre
       a.items_dev = (const Item*)(dev + kTableJobs * sizeof(Job));
       a.n_items = (int)items.size();
       a.total = a.n_items * a.bx * a.by;
-      e = launch_fused(c0->d.wavelet, c0->d.format, c0->variant, a, c0->n_cu, s);
+      e = launch_fused(c0->d.wavelet, c0->d.format, variant, a, c0->n_cu, s);
       if (e != hipSuccess) return hip_fail(e, "fused batch launch");
       e = hipEventRecord(c0->tab_done[slot], s);
       if (e != hipSuccess) return hip_fail(e, "batch table event");
@@ -600,15 +609,13 @@ extern "C" wv_status wv_autotune(wv_ctx* c, int32_t n_visible, int32_t reps, hip
     job.flags = kJobHasOut;
     std::vector<Item> items(n_visible);
     for (int i = 0; i < n_visible; ++i) items[i] = Item{(uint16_t)i, (uint16_t)i, 0, (uint8_t)d.levels, 0};
-    const int saved = c->variant;
     for (int v = 0; v < wv_variant_count(c) && e == hipSuccess; ++v) {
       if (!variant_fits(d, fused_variant(d.wavelet, d.format, v))) continue;
-      c->variant = v;
       wv_status st = WV_OK;
-      for (int w = 0; w < 2 && st == WV_OK; ++w) st = launch_arg_chunks(c, &job, 1, items, s);
+      for (int w = 0; w < 2 && st == WV_OK; ++w) st = launch_arg_chunks(c, v, &job, 1, items, s);
       if (st == WV_OK) e = hipEventRecord(t0, s);
       for (int r = 0; r < reps && st == WV_OK && e == hipSuccess; ++r)
-        st = launch_arg_chunks(c, &job, 1, items, s);
+        st = launch_arg_chunks(c, v, &job, 1, items, s);
       if (st != WV_OK) { e = hipErrorLaunchFailure; break; }
       if (e == hipSuccess) e = hipEventRecord(t1, s);
       if (e == hipSuccess) e = hipEventSynchronize(t1);
@@ -619,7 +626,10 @@ extern "C" wv_status wv_autotune(wv_ctx* c, int32_t n_visible, int32_t reps, hip
         best = v;
       }
     }
-    c->variant = best >= 0 ? best : saved;
+    if (best >= 0) {
+      c->variant = best;
+      c->few_variant = -1;
+    }
   }
   if (t0) hipEventDestroy(t0);
   if (t1) hipEventDestroy(t1);

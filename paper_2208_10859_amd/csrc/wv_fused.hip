@@ -417,10 +417,9 @@ const Variant* fused_variant(int, int, int v) {
 // resident units per CU hide each other's latency, against the 32-row phased
 // ones that come first (us, five levels, 1 and 36 tiles): a 5/3 frame 13.7 -> 9.0
 // and 23.0 -> 21.6, its GOP of 8 88.3 -> 52.4 and 160.9 -> 148.3; a 9/7 frame
-// 22.0 -> 15.2 and 80.3 -> 53.9, its GOP 159.8 -> 104.6 and 684.4 -> 492.4.  Grey
-// frames have no chroma chains to run beside the luma one, and the 32-row form
-// stays the better one there (36 tiles: a 5/3 frame 14.5 against 15.5, a 9/7
-// frame 34.0 against 35.6).
+// 22.0 -> 15.2 and 80.3 -> 53.9, its GOP 159.8 -> 104.6 and 684.4 -> 492.4; 256
+// tiles: 147.3 -> 129.2 and 509.6 -> 368.1.  Grey frames have no chroma chains to
+// run beside the luma one: the 32-row form stays, but for few tiles (below).
 int default_variant(const wv_desc& d) {
   for (int v = 0; v < kNumVariants; ++v) {
     const Variant& var = kVariants[v];
@@ -429,6 +428,20 @@ int default_variant(const wv_desc& d) {
   }
   for (int v = 0; v < kNumVariants; ++v)
     if (wvp::variant_fits(d, &kVariants[v])) return v;
+  return -1;
+}
+
+// Grey 5/3 frames of 512-sample tiles: up to 24 tiles the 32-row strips leave
+// CUs idle and the 16-row chain strips are faster (us, three levels: a frame of
+// 1 / 6 / 24 tiles 7.8 -> 6.4, 7.8 -> 6.8, 9.9 -> 9.6, a GOP of 8 39.7 -> 30.8,
+// 42.8 -> 32.4, 56.8 -> 49.5); beyond, they are slower (120 tiles: 27.1 against
+// 29.9).  9/7: 10.7 / 10.6, 12.3 / 12.6, and 15.8 / 18.4 at 16 tiles, so never.
+int few_tiles_variant(const wv_desc& d) {
+  if (d.format != WV_GRAY8 || d.wavelet != WV_W53) return -1;
+  for (int v = 0; v < kNumVariants; ++v) {
+    const Variant& var = kVariants[v];
+    if (var.kind == 2 && var.bw == 512 && var.shape == 4 && !var.persistent && wvp::variant_fits(d, &var)) return v;
+  }
   return -1;
 }
 

@@ -79,3 +79,33 @@ def test_sets_still_need_512_sample_tiles():
         with pytest.raises(wv.WvError) as e:
             dec.decode_set(bands, 2, (1, 1), 0, np.ones(2, np.uint8), [out])
         assert e.value.status == wv.EUNSUPPORTED
+
+
+def test_grey_calls_of_few_and_of_many_tiles():
+    """Grey 5/3 frames of 512-sample tiles take another variant up to 24 tiles:
+    both sides of the line give the same bytes as a chosen variant, and a
+    choice holds for every call."""
+    from paper_2208_10859_amd import wv
+    dec = wv.Decoder(5 * 512, 5 * 512, 512, 3, wv.W53, wv.GRAY8)
+    first = dec.variant
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    coef = [torch.randint(-40, 40, dec.plane_shape(0), generator=gen, device="cuda", dtype=torch.int16)]
+    for n_vis in (24, 25):
+        mask = np.zeros(25, np.uint8)
+        mask[:n_vis] = 1
+        res = []
+        for pick in (None, first, dec.variants().index("strip_r16_w4_L3_chain_grid")):
+            d = wv.Decoder(5 * 512, 5 * 512, 512, 3, wv.W53, wv.GRAY8)
+            if pick is not None:
+                d.variant = pick
+            ref = wv.Reference(d)
+            outs = [torch.empty(d.out_shape(n_vis), dtype=torch.uint8, device="cuda") for _ in range(3)]
+            d.decode_viewport(coef, 0, True, 3, mask, ref, outs[0])
+            d.decode_gop([(coef, False, 1), (coef, False, 2)], 1, mask, ref, outs[1:])
+            assert pick is None or d.variant == pick
+            torch.cuda.synchronize()
+            res.append(outs + [ref.planes[0]])
+        for r in res[1:]:
+            for a, b in zip(r, res[0]):
+                assert torch.equal(a, b)
