@@ -160,9 +160,9 @@ wv_status wv_decode_viewport_noalloc(const wv_desc* desc, const wv_frame* coeffs
  * be frames[0].frame_index + f; the same tile_mask and level_count apply to
  * every frame; the first frame obeys wv_decode_viewport's stamp rule.
  * outs: HOST array [n_frames] of device outputs (entries may be NULL), or
- * NULL.  With a row-strip variant the frames go in one launch (per group of
- * 8 frames): every tile strip is taken through the frames in order, so
- * workgroups need not wait for each other between frames.  Other forms
+ * NULL.  With a row-strip or whole-tile variant the frames go in one launch
+ * (per group of 8 frames): every tile (strip) is taken through the frames in
+ * order, so workgroups need not wait for each other between frames.  Other forms
  * decode frame by frame.  On success the masked tiles' stamps become the
  * last frame's index.  Errors: as wv_decode_viewport. */
 wv_status wv_decode_gop(wv_ctx* ctx, int32_t n_frames, const wv_frame* frames,
@@ -257,7 +257,8 @@ wv_status wv_foveation_levels(const wv_desc* desc, double yaw, double pitch, dou
  * int16 indices (5/3) or float32 values qstep*q (9/7, computed in float64).
  * Synchronises the stream.  The first call of a context with tiles of 256 or
  * 512 samples and more than two levels allocates a workspace (at most half a
- * byte per sample for 5/3, one for 9/7) that the context keeps.
+ * byte per sample for 5/3, one for 9/7) that the context keeps; calls of
+ * several threads on one context take turns.
  * Errors: WV_EINVAL (NULL planes, qstep < 1, an index outside int16),
  * WV_ENOMEM, WV_EDEVICE. */
 wv_status wv_encode_intra(wv_ctx* ctx, const void* const* src, void* const* coeffs,
@@ -271,7 +272,9 @@ wv_status wv_encode_intra(wv_ctx* ctx, const void* const* src, void* const* coef
 wv_status wv_autotune(wv_ctx* ctx, int32_t n_visible, int32_t reps, hipStream_t stream,
                       int32_t* best_variant);
 
-/* Number of fused variants, and the one in use; select one by index. */
+/* Number of fused variants, and the one in use; select one by index.  Until
+ * one is selected or tuned, calls of few visible tiles may run in another
+ * variant that is faster for them; then the chosen one runs for every call. */
 int32_t wv_variant_count(const wv_ctx* ctx);
 wv_status wv_get_variant(const wv_ctx* ctx, int32_t* variant);
 wv_status wv_set_variant(wv_ctx* ctx, int32_t variant);

@@ -97,7 +97,6 @@ wv_status wv_create(wv_ctx** out, const wv_desc* desc) {
   if (e == hipSuccess) e = hipHostMalloc((void**)&c->tab_host, kTableSlots * kTableBytes + sizeof(int), hipHostMallocDefault);
   if (e == hipSuccess) {
     c->enc_flag = (int*)(c->tab_host + kTableSlots * kTableBytes);
-    *c->enc_flag = 0;
   }
   if (e == hipSuccess) e = hipMalloc((void**)&c->tab_dev, kTableSlots * kTableBytes);
   for (int i = 0; e == hipSuccess && i < kTableSlots; ++i)
@@ -551,6 +550,7 @@ extern "C" wv_status wv_encode_intra(wv_ctx* c, const void* const* src, void* co
   for (int p = 0; p < c->nplanes; ++p)
     if (!src[p] || !coeffs[p]) return fail(WV_EINVAL, "plane %d pointer is NULL", p);
   const size_t bytes = encode_workspace_bytes(c->d.wavelet, c->nplanes, c->n_tiles, c->d.tile, c->d.levels);
+  std::lock_guard<std::mutex> lock(c->enc_mu);
   if (bytes && !c->enc_ws) {
     const hipError_t e = hipMalloc(&c->enc_ws, bytes);
     if (e != hipSuccess) {
@@ -558,14 +558,12 @@ extern "C" wv_status wv_encode_intra(wv_ctx* c, const void* const* src, void* co
       return fail(WV_ENOMEM, "encoder workspace: %s", hipGetErrorString(e));
     }
   }
+  *c->enc_flag = 0;
   hipError_t e = launch_encode(c->d.wavelet, c->nplanes, c->n_tiles, c->d.tile, c->d.levels, qstep, src,
                                coeffs, c->enc_ws, c->enc_flag, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "wv_encode_intra");
-  if (*(volatile int*)c->enc_flag) {
-    *c->enc_flag = 0;
-    return fail(WV_EINVAL, "a quantisation index falls outside int16 (raise qstep)");
-  }
+  if (*(volatile int*)c->enc_flag) return fail(WV_EINVAL, "a quantisation index falls outside int16 (raise qstep)");
   return WV_OK;
 }
 

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <mutex>
 #include <vector>
 
 #include "wv_internal.h"
@@ -45,7 +46,9 @@ struct wv_ctx {
   int tab_next = 0;
   // encoder: device workspace (allocated by the first call that needs one,
   // kept until the context is destroyed) and overflow flag (pinned, the tail
-  // of tab_host; 0 between calls)
+  // of tab_host).  A call holds enc_mu from its launches to its
+  // synchronisation: calls of several threads or streams take turns.
+  std::mutex enc_mu;
   void* enc_ws = nullptr;
   int* enc_flag = nullptr;
 };

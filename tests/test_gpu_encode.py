@@ -45,3 +45,36 @@ def test_encoder_matches_oracle(tile, levels, grey, wavelet):
                 # tie may land on the next multiple of the step
                 diff = np.abs(got.astype(np.float64) - w)
                 assert diff.max() <= step and np.mean(diff > 0) < 1e-4
+
+
+@pytest.mark.parametrize("wavelet", [owv.W53, owv.W97])
+def test_threads_share_one_context(wavelet):
+    """The context's workspace serves one call at a time: two threads with
+    streams and planes of their own get what each gets alone."""
+    import threading
+
+    from paper_2208_10859_amd import wv
+    dec = wv.Decoder(2048, 1024, 256, 4, wv.W53 if wavelet == owv.W53 else wv.W97, wv.GRAY8)
+    torch.manual_seed(1)
+    src = [torch.randint(0, 256, dec.plane_shape(0), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    alone, dst = [[torch.zeros(dec.plane_shape(0), dtype=dec.coef_dtype, device="cuda") for _ in range(2)]
+                  for _ in range(2)]
+    for s, d in zip(src, alone):
+        dec.encode_intra([s], [d], 2)
+    torch.cuda.synchronize()
+    same = [[], []]
+
+    def work(k):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            for _ in range(20):
+                dst[k].zero_()
+                dec.encode_intra([src[k]], [dst[k]], 2, stream=st)
+                same[k].append(torch.equal(dst[k], alone[k]))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert same == [[True] * 20] * 2
