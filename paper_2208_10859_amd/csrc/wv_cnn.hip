@@ -32,24 +32,14 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 
 constexpr int kpad16(int cin) { return (9 * cin + 15) / 16 * 16; }
 
-// The backward data pass of one layer (the convolution of the output
-// gradient with the flipped, transposed kernel, masked by the layer's ReLU)
-// as an implicit GEMM on gfx950's
-// v_mfma_f32_16x16x32_bf16: M = output channels (16 per MFMA), N = pixels
-// (16 consecutive columns of one row), K = 9 taps x input channels,
-// tap-major, padded to a multiple of 32.  For 32 input channels one K step is
-// one tap; for 4 it is 8 taps.  MFMA 16x16x32 operands: lane l supplies
-// A[l % 16][8 (l / 16) + q] and B[8 (l / 16) + q][l % 16], q = 0..7 (any
-// pairing of K positions works as long as A and B use the same one), and
-// receives D[4 (l / 16) + q][l % 16]: four consecutive output channels of
-// one pixel, stored as one 8-byte write.
-// A workgroup computes a 16 x 32 pixel block; wave w owns rows 4w .. 4w+3.  Each wave holds the layer's whole weight matrix
-// in registers (18 operands of 8 bf16 for 32 -> 32), loaded once; the input
-// patch with its one-pixel border is staged in LDS, for 32 channels as four
-// planes of 8-channel (16-byte) pixels so that the 16 lanes of an operand
-// read 16 consecutive 16-byte words.
-//   out = bf16(aux > 0 ? acc : 0)   [pixels][COUT]   (aux: the layer's input activation)
-constexpr int CH = 16, CW = 32;           // output pixels per workgroup: 16 rows x 32 columns
+// Convolutions are implicit GEMMs on gfx950's v_mfma_f32_16x16x32_bf16: M =
+// output channels (16 per MFMA), N = pixels (16 consecutive columns of one
+// row), K = 9 taps x input channels, tap-major, padded to a multiple of 32.
+// For 32 input channels one K step is one tap; for 4 it is 8 taps.  MFMA
+// 16x16x32 operands: lane l supplies A[l % 16][8 (l / 16) + q] and
+// B[8 (l / 16) + q][l % 16], q = 0..7 (any pairing of K positions works as long
+// as A and B use the same one), and receives D[4 (l / 16) + q][l % 16]: four
+// consecutive output channels of one pixel, stored as one 8-byte write.
 constexpr int kpad32(int cin) { return (9 * cin + 31) / 32 * 32; }
 
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
@@ -64,152 +54,10 @@ __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{a, b}, bf2));
 }
 
-template <int CIN, int COUT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv(const uint16_t* __restrict__ x,
-                                              const uint16_t* __restrict__ wt,
-                                              const uint16_t* __restrict__ aux, uint16_t* __restrict__ out,
-                                              int N, int H, int W) {
-  static_assert(CIN == 4 || CIN == 32, "input channels: 4 or 32");
-  constexpr int KP = kpad32(CIN), KS = KP / 32, NB = COUT / 16;
-  constexpr int PW = CW + 2, PH = CH + 2, PLANE = PH * PW + 1;
-  constexpr int LDS_BYTES = CIN == 32 ? 4 * PLANE * 16 : PH * PW * 8;
-  __shared__ __align__(16) unsigned char lds[LDS_BYTES];
-  const int nbx = (W + CW - 1) / CW, nby = (H + CH - 1) / CH;
-  const int bx = blockIdx.x % nbx, by = (blockIdx.x / nbx) % nby, n = blockIdx.x / (nbx * nby);
-  const int y0 = by * CH, x0 = bx * CW;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i16 = lane & 15, g = lane >> 4;
-
-  // the weight matrix, in registers for the whole block
-  bf8 wr[KS][NB];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-      wr[ks][nb] = as_bf8(*(const uint4*)(wt + (nb * 16 + i16) * KP + ks * 32 + 8 * g));
-
-  // input patch with a one-pixel border (zero outside the image); every
-  // global read is issued before the LDS writes, so that the staging waits
-  // for memory once
-  if constexpr (CIN == 32) {
-    constexpr int NI = PH * PW * 4, NIT = (NI + 255) / 256;
-    uint4 pv[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int idx = tid + 256 * it, p = idx >> 2, c = idx & 3;
-      const int pr = p / PW, pc = p - pr * PW;
-      const int gy = y0 + pr - 1, gx = x0 + pc - 1;
-      pv[it] = make_uint4(0u, 0u, 0u, 0u);
-      if (idx < NI && gy >= 0 && gy < H && gx >= 0 && gx < W)
-        pv[it] = *(const uint4*)(x + ((size_t)(n * H + gy) * W + gx) * 32 + c * 8);
-    }
-    uint4* p16 = (uint4*)lds;
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int idx = tid + 256 * it;
-      if (idx < NI) p16[(idx & 3) * PLANE + (idx >> 2)] = pv[it];
-    }
-  } else {
-    constexpr int NI = PH * PW, NIT = (NI + 255) / 256;
-    uint2 pv[NIT];
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int p = tid + 256 * it, pr = p / PW, pc = p - pr * PW;
-      const int gy = y0 + pr - 1, gx = x0 + pc - 1;
-      pv[it] = make_uint2(0u, 0u);
-      if (p < NI && gy >= 0 && gy < H && gx >= 0 && gx < W)
-        pv[it] = *(const uint2*)(x + ((size_t)(n * H + gy) * W + gx) * 4);
-    }
-    uint2* p8 = (uint2*)lds;
-#pragma unroll
-    for (int it = 0; it < NIT; ++it) {
-      const int p = tid + 256 * it;
-      if (p < NI) p8[p] = pv[it];
-    }
-  }
-  __syncthreads();
-
-  // Wave w's rows 4 w .. 4 w + 3, one 16-column block after the other; the
-  // mask's words arrive while the products run.
-  uint2 mask[2][4][NB];
-#pragma unroll
-  for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int gy = y0 + 4 * wave + r, gx = x0 + cb * 16 + i16;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        mask[cb][r][nb] = make_uint2(0u, 0u);
-        if (gy < H && gx < W)
-          mask[cb][r][nb] = *(const uint2*)(aux + ((size_t)(n * H + gy) * W + gx) * COUT + nb * 16 + 4 * g);
-      }
-    }
-#pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
-    f4 acc[4][NB];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) acc[r][nb] = f4{0.f, 0.f, 0.f, 0.f};
-    if constexpr (CIN == 32) {
-      // an input row's operand serves the three output rows it reaches (per
-      // output the taps come in the order (ky, kx))
-      const uint4* p = (const uint4*)lds + g * PLANE + 4 * wave * PW + cb * 16 + i16;
-#pragma unroll
-      for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int kx = 0; kx < 3; ++kx) {
-          const bf8 b = as_bf8(p[i * PW + kx]);
-#pragma unroll
-          for (int ky = 0; ky < 3; ++ky) {
-            const int r = i - ky;
-            if (r < 0 || r >= 4) continue;
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-              acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[ky * 3 + kx][nb], b, acc[r][nb], 0, 0, 0);
-          }
-        }
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          // taps t0 = 8 ks + 2 g and t0 + 1, four channels each; taps >= 9 are zero
-          const uint2* p8 = (const uint2*)lds + (4 * wave + r) * PW + cb * 16 + i16;
-          const int t0 = ks * 8 + 2 * g, t1 = t0 + 1;
-          const int u0 = min(t0, 8), u1 = min(t1, 8);
-          uint2 lo = p8[(u0 / 3) * PW + u0 % 3];
-          uint2 hi = p8[(u1 / 3) * PW + u1 % 3];
-          if (t0 >= 9) lo = make_uint2(0u, 0u);
-          if (t1 >= 9) hi = make_uint2(0u, 0u);
-          const bf8 b = as_bf8(make_uint4(lo.x, lo.y, hi.x, hi.y));
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            acc[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[ks][nb], b, acc[r][nb], 0, 0, 0);
-        }
-    }
-    // epilogue: lane (g, i16) holds channels nb * 16 + 4 g .. + 3 of pixel i16
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int gy = y0 + 4 * wave + r, gx = x0 + cb * 16 + i16;
-      if (gy >= H || gx >= W) continue;
-      const size_t px = (size_t)(n * H + gy) * W + gx;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        const uint2 m = mask[cb][r][nb];
-        const uint16_t mh[4] = {(uint16_t)m.x, (uint16_t)(m.x >> 16), (uint16_t)m.y, (uint16_t)(m.y >> 16)};
-        float v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = bf2f(mh[q]) > 0.f ? acc[r][nb][q] : 0.f;
-        *(uint2*)(out + px * COUT + nb * 16 + 4 * g) = make_uint2(pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3]));
-      }
-    }
-  }
-}
-
 // Weight and bias gradients of one layer: dW[o][tap][i] = sum over pixels of
 // dy[p][o] x[p + tap offset][i], as a GEMM with M = output channels, N = 9
 // taps x input channels (padded to 16), K = pixels, on
-// v_mfma_f32_16x16x32_bf16 (operand layout as in k_conv).  This kernel: the
+// v_mfma_f32_16x16x32_bf16 (operands as above).  This kernel: the
 // first layer (image with 4 channels in memory, 3 real, dy with 32).  A
 // workgroup stages the transposed dy of an 8 x 32 block and three
 // column-shifted, channel-major copies of the input patch (so that four
@@ -387,22 +235,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   if (tid < COUTR) row_out[NW + tid] = bred[0][tid] + bred[1][tid] + bred[2][tid] + bred[3][tid];
 }
 
-// Weight and bias gradients of the layers with 32 input channels, the same
-// GEMM.  Both operands are channels x pixels, the transpose of what memory
-// holds; the staged pixels stay as they are, [16-channel half][pixel][16], and
-// the operands are read with the LDS's transposing read
-// (ds_read_b64_tr_b16: of 16 lanes, lane s addresses 4 channels of a pixel,
-// pixel s / 4, channels 4 (s % 4) .. + 3, and receives channel s of the four
-// pixels), two per operand.  A workgroup stages 16 x 32 pixel blocks, the next
-// one's global reads under way while one is multiplied.  Wave w takes input
-// channels 16 (w % 2) .. and four rows of the block, and streams down the x
-// rows: an x operand serves the three taps (ky) that reach the wave's dy rows,
-// which stay in registers.  The bias gradient is the product with a column of
-// ones.  The four waves of a channel half are summed in LDS at the end.
+// Backward pass of a layer with 32 input channels: its weight and bias
+// gradients (the same GEMM), and the gradient of its input dx (the convolution
+// of dy with the flipped, transposed kernel, masked by the ReLU that made the
+// input x: dx = bf16(x > 0 ? sum : 0)).  Both need the block of x and of dy with
+// a border, so one kernel stages them once; of its eight waves four compute
+// each, one of either kind on every SIMD.
+// A workgroup stages 16 x 32 pixel blocks, the next one's global reads under way
+// while one is multiplied.  The staged pixels stay as they are in memory,
+// [16-channel half][pixel][16].
+// Weight gradient: both operands are channels x pixels, the transpose of that,
+// and are read with the LDS's transposing read (ds_read_b64_tr_b16: of 16
+// lanes, lane s addresses 4 channels of a pixel, pixel s / 4, channels 4 (s % 4)
+// .. + 3, and receives channel s of the four pixels), two per operand.  Wave w
+// takes input channels 16 (w % 2) .. and eight rows of the block, four at a time,
+// and streams down the x rows: an x operand serves the three taps (ky) that
+// reach the wave's dy rows, which stay in registers.  The bias gradient is the
+// product with a column of ones.  The two waves of a channel half are summed in
+// LDS at the end.
+// Data gradient: wave w takes rows 4 (w - 4) .. + 3, the whole weight matrix in
+// registers (18 operands of 8 bf16), loaded once.
 // What bounds it: the latency of its two rounds of global reads, then their
-// bytes.  16 x 128 x 128, 32 dy channels: 19.4 -> 14.7 us (33.5 MB, 6.5 us at a
-// copy's rate), 3 dy channels: 14.9 -> 12.4 us, against transposed copies
-// written to LDS a word at a time.  Reads two blocks ahead: 16.2.
+// bytes (16 x 128 x 128, 32 dy channels: 50 MB, 9.6 us at a copy's rate).
+// There, 32 dy channels: 21 us; as two kernels 27.8 us (14.9 weights, 12.9
+// data), 3 dy channels: 14.2 us against 10.4 + 9.7.  With every wave doing both
+// parts in turn the registers ran out (23 and 14.9 us).  Weight gradients
+// from transposed copies written to LDS a word at a time took 19.4 us.
 //   DYC: dy channels in memory (32, or 4 of which 3 are real).
 constexpr int GH = 16, GW = 32;           // block of pixels
 constexpr int GWAVES = 8;
@@ -417,50 +275,165 @@ __device__ __forceinline__ bf8 tr_operand(const uint16_t* p) {
 
 template <int DYC>
 __global__ __launch_bounds__(64 * GWAVES) __attribute__((amdgpu_waves_per_eu(2)))
-void k_wgrad32(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, float* __restrict__ part, int width,
-               int N, int H, int W, int bpw) {
+void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, const uint16_t* __restrict__ wt,
+            uint16_t* __restrict__ dx, float* __restrict__ part, int width, int N, int H, int W, int bpw) {
   constexpr int MB = DYC == 32 ? 2 : 1, COUTR = DYC == 32 ? 32 : 3, NW = COUTR * 9 * 32, NT = 64 * GWAVES;
-  constexpr int XPX = (GH + 2) * (GW + 2), DPX = GH * GW;      // staged pixels
+  constexpr int PW = GW + 2, XPX = (GH + 2) * PW;               // staged pixels: the block and its border
   constexpr int NACC = 9 * MB + MB;                             // accumulator tiles of a wave
-  constexpr int STAGE = (2 * XPX + MB * DPX) * 16 * 2, REDUCE = GWAVES / 2 * NACC * 64 * 16;
+  constexpr int KP = kpad32(DYC), KS = KP / 32;                 // the data gradient's K steps
+  constexpr int STAGE = (2 + MB) * XPX * 16 * 2 + (DYC == 32 ? 0 : XPX * 8), REDUCE = 2 * NACC * 64 * 16;
   __shared__ __align__(16) unsigned char lds[STAGE > REDUCE ? STAGE : REDUCE];
   uint16_t* xs = (uint16_t*)lds;               // [2][XPX][16]
-  uint16_t* ds = xs + 2 * XPX * 16;            // [MB][DPX][16]
+  uint16_t* ds = xs + 2 * XPX * 16;            // [MB][XPX][16]
+  uint2* d4 = (uint2*)(ds + MB * XPX * 16);    // DYC = 4: [XPX][4]
   const int nbx = (W + GW - 1) / GW, nby = (H + GH - 1) / GH, nblocks = nbx * nby * N;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int i16 = lane & 15, g = lane >> 4, ib = wave & 1, rq = wave >> 1;
+  const int i16 = lane & 15, g = lane >> 4;
   // this lane's part of an operand's first 16 pixels
   const int tr = (4 * g + (i16 >> 2)) * 16 + 4 * (i16 & 3);
 
-  constexpr int NX = (XPX * 4 + NT - 1) / NT, ND = DYC == 32 ? DPX * 4 / NT : (DPX + NT - 1) / NT;
+  constexpr int NX = (XPX * 4 + NT - 1) / NT, ND = DYC == 32 ? NX : (XPX + NT - 1) / NT;
   uint4 xv[NX], dv[ND];
   auto load = [&](int blk) __attribute__((always_inline)) {
     const int bx = blk % nbx, by = (blk / nbx) % nby, n = blk / (nbx * nby);
 #pragma unroll
     for (int it = 0; it < NX; ++it) {
-      const int idx = tid + NT * it, px = idx >> 2, r = px / (GW + 2), c = px - r * (GW + 2);
+      const int idx = tid + NT * it, px = idx >> 2, r = px / PW, c = px - r * PW;
       const int gy = by * GH + r - 1, gx = bx * GW + c - 1;
       xv[it] = make_uint4(0u, 0u, 0u, 0u);
-      if (idx < XPX * 4 && gy >= 0 && gy < H && gx >= 0 && gx < W)
-        xv[it] = *(const uint4*)(x + ((size_t)(n * H + gy) * W + gx) * 32 + (idx & 3) * 8);
+      if constexpr (DYC == 32) dv[it] = make_uint4(0u, 0u, 0u, 0u);
+      if (idx < XPX * 4 && gy >= 0 && gy < H && gx >= 0 && gx < W) {
+        const size_t e = ((size_t)(n * H + gy) * W + gx) * 32 + (idx & 3) * 8;
+        xv[it] = *(const uint4*)(x + e);
+        if constexpr (DYC == 32) dv[it] = *(const uint4*)(dy + e);
+      }
     }
+    if constexpr (DYC != 32) {
 #pragma unroll
-    for (int it = 0; it < ND; ++it) {
-      const int idx = tid + NT * it, px = DYC == 32 ? idx >> 2 : idx;
-      const int gy = by * GH + px / GW, gx = bx * GW + px % GW;
-      dv[it] = make_uint4(0u, 0u, 0u, 0u);
-      if (px < DPX && gy < H && gx < W) {
-        const size_t e = (size_t)(n * H + gy) * W + gx;
-        if constexpr (DYC == 32) {
-          dv[it] = *(const uint4*)(dy + e * 32 + (idx & 3) * 8);
-        } else {
-          const uint2 v = *(const uint2*)(dy + e * 4);
-          dv[it] = make_uint4(v.x, v.y & 0xffffu, 0u, 0u);   // three real channels
+      for (int it = 0; it < ND; ++it) {
+        const int px = tid + NT * it, r = px / PW, c = px - r * PW;
+        const int gy = by * GH + r - 1, gx = bx * GW + c - 1;
+        dv[it] = make_uint4(0u, 0u, 0u, 0u);
+        if (px < XPX && gy >= 0 && gy < H && gx >= 0 && gx < W) {
+          const uint2 v = *(const uint2*)(dy + ((size_t)(n * H + gy) * W + gx) * 4);
+          dv[it] = make_uint4(v.x, v.y, 0u, 0u);
         }
       }
     }
   };
 
+  const int blk0 = blockIdx.x * bpw, blk1 = min(blk0 + bpw, nblocks);
+  // a block into LDS, and the next one's reads under way
+  auto stage = [&](int blk) __attribute__((always_inline)) {
+    if (blk > blk0) __syncthreads();   // the previous block's operands are read
+#pragma unroll
+    for (int it = 0; it < NX; ++it) {
+      const int idx = tid + NT * it, at = ((idx & 3) >> 1) * (XPX * 16) + (idx >> 2) * 16 + (idx & 1) * 8;
+      if (idx < XPX * 4) {
+        *(uint4*)(xs + at) = xv[it];
+        if constexpr (DYC == 32) *(uint4*)(ds + at) = dv[it];
+      }
+    }
+    if constexpr (DYC != 32) {
+#pragma unroll
+      for (int it = 0; it < ND; ++it) {
+        const int px = tid + NT * it;
+        if (px < XPX) {
+          d4[px] = make_uint2(dv[it].x, dv[it].y);
+          *(uint4*)(ds + px * 16) = make_uint4(dv[it].x, dv[it].y & 0xffffu, 0u, 0u);   // three real channels
+          *(uint4*)(ds + px * 16 + 8) = make_uint4(0u, 0u, 0u, 0u);
+        }
+      }
+    }
+    __syncthreads();
+    if (blk + 1 < blk1) load(blk + 1);
+  };
+  load(blk0);
+  // The waves' parts have loops of their own (with one loop both parts' registers
+  // would be held); their barriers pair up.
+  if (wave >= 4) {
+    // data gradient
+    const int cr = 4 * (wave - 4);   // first row
+    bf8 wr[KS][2];   // the weight matrix
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb) wr[ks][nb] = as_bf8(*(const uint4*)(wt + (nb * 16 + i16) * KP + ks * 32 + 8 * g));
+    for (int blk = blk0; blk < blk1; ++blk) {
+      stage(blk);
+      // this wave's four rows, 16 columns at a time
+      const int bx = blk % nbx, by = (blk / nbx) % nby, n = blk / (nbx * nby);
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        f4 o[4][2];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb) o[r][nb] = f4{0.f, 0.f, 0.f, 0.f};
+        const int p0 = cr * PW + cb * 16 + i16;   // the lane's pixel of the first row, tap (0, 0)
+        if constexpr (DYC == 32) {
+          // an input row's operand serves the three output rows it reaches (per
+          // output the taps come in the order (ky, kx))
+          const uint16_t* p = ds + ((g >> 1) * XPX + p0) * 16 + (g & 1) * 8;
+#pragma unroll
+          for (int i = 0; i < 6; ++i)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+              const bf8 b = as_bf8(*(const uint4*)(p + (i * PW + kx) * 16));
+#pragma unroll
+              for (int ky = 0; ky < 3; ++ky) {
+                const int r = i - ky;
+                if (r < 0 || r >= 4) continue;
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+                  o[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[ky * 3 + kx][nb], b, o[r][nb], 0, 0, 0);
+              }
+            }
+        } else {
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              // taps t0 = 8 ks + 2 g and t0 + 1, four channels each; taps >= 9 are zero
+              const uint2* p8 = d4 + p0 + r * PW;
+              const int t0 = ks * 8 + 2 * g, t1 = t0 + 1;
+              const int u0 = min(t0, 8), u1 = min(t1, 8);
+              uint2 lo = p8[(u0 / 3) * PW + u0 % 3];
+              uint2 hi = p8[(u1 / 3) * PW + u1 % 3];
+              if (t0 >= 9) lo = make_uint2(0u, 0u);
+              if (t1 >= 9) hi = make_uint2(0u, 0u);
+              const bf8 b = as_bf8(make_uint4(lo.x, lo.y, hi.x, hi.y));
+#pragma unroll
+              for (int nb = 0; nb < 2; ++nb)
+                o[r][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[ks][nb], b, o[r][nb], 0, 0, 0);
+            }
+        }
+        // lane (g, i16) holds channels nb * 16 + 4 g .. + 3 of pixel i16; the
+        // mask is the staged activation
+        const int gx = bx * GW + cb * 16 + i16;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int gy = by * GH + cr + r;
+          if (gy >= H || gx >= W) continue;
+          const size_t px = (size_t)(n * H + gy) * W + gx;
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb) {
+            const uint2 m = *(const uint2*)(xs + (nb * XPX + p0 + (r + 1) * PW + 1) * 16 + 4 * g);
+            const uint16_t mh[4] = {(uint16_t)m.x, (uint16_t)(m.x >> 16), (uint16_t)m.y, (uint16_t)(m.y >> 16)};
+            float v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] = bf2f(mh[q]) > 0.f ? o[r][nb][q] : 0.f;
+            *(uint2*)(dx + px * 32 + nb * 16 + 4 * g) = make_uint2(pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3]));
+          }
+        }
+      }
+    }
+    __syncthreads();
+    __syncthreads();
+    return;
+  }
+  // weight gradient
+  const int ib = wave & 1, rh = wave >> 1;   // input channel half, row half
   f4 acc[9][MB], accb[MB];
 #pragma unroll
   for (int m = 0; m < MB; ++m) {
@@ -470,79 +443,58 @@ void k_wgrad32(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, 
   }
   const uint32_t one2 = 0x3f803f80u;
   const bf8 ones = as_bf8(make_uint4(one2, one2, one2, one2));
-  const int blk0 = blockIdx.x * bpw, blk1 = min(blk0 + bpw, nblocks);
-  load(blk0);
   for (int blk = blk0; blk < blk1; ++blk) {
-    if (blk > blk0) __syncthreads();   // the previous block's operands are read
+    stage(blk);
+    // eight rows of the block, four at a time
 #pragma unroll
-    for (int it = 0; it < NX; ++it) {
-      const int idx = tid + NT * it;
-      if (idx < XPX * 4) *(uint4*)(xs + ((idx & 3) >> 1) * (XPX * 16) + (idx >> 2) * 16 + (idx & 1) * 8) = xv[it];
-    }
-#pragma unroll
-    for (int it = 0; it < ND; ++it) {
-      const int idx = tid + NT * it;
-      if constexpr (DYC == 32) {
-        *(uint4*)(ds + ((idx & 3) >> 1) * (DPX * 16) + (idx >> 2) * 16 + (idx & 1) * 8) = dv[it];
-      } else if (idx < DPX) {
-        *(uint4*)(ds + idx * 16) = dv[it];
-        *(uint4*)(ds + idx * 16 + 8) = make_uint4(0u, 0u, 0u, 0u);
-      }
-    }
-    __syncthreads();
-    if (blk + 1 < blk1) load(blk + 1);
-    bf8 a[4][MB];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int m = 0; m < MB; ++m) a[r][m] = tr_operand(ds + (m * DPX + (4 * rq + r) * GW) * 16 + tr);
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-      for (int kx = 0; kx < 3; ++kx) {
-        const bf8 b = tr_operand(xs + (ib * XPX + (4 * rq + i) * (GW + 2) + kx) * 16 + tr);
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) {
-          const int r = i - ky;
-          if (r < 0 || r >= 4) continue;
-#pragma unroll
-          for (int m = 0; m < MB; ++m)
-            acc[ky * 3 + kx][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r][m], b, acc[ky * 3 + kx][m], 0, 0, 0);
-        }
-      }
-    if (ib == 0)
+    for (int half = 0; half < 2; ++half) {
+      const int y4 = 8 * rh + 4 * half;
+      bf8 a[4][MB];
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int m = 0; m < MB; ++m) accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r][m], ones, accb[m], 0, 0, 0);
-  }
-  // the four row quarters of each channel half: 1 into 0 and 3 into 2, then 2 into 0
-  f4* red = (f4*)lds;
+        for (int m = 0; m < MB; ++m) a[r][m] = tr_operand(ds + (m * XPX + (y4 + r + 1) * PW + 1) * 16 + tr);
 #pragma unroll
-  for (int step = 1; step <= 2; ++step) {
-    __syncthreads();
-    const bool gives = step == 1 ? rq & 1 : rq == 2, takes = step == 1 ? !(rq & 1) : rq == 0;
-    f4* slot = red + (size_t)((rq >> 1) * 2 + ib) * NACC * 64 + lane;    // of the pair (rq, rq ^ 1)
-    f4* from = step == 1 ? slot : red + (size_t)ib * NACC * 64 + lane;
-    if (gives) {
+      for (int i = 0; i < 6; ++i)
 #pragma unroll
-      for (int t = 0; t < 9; ++t)
+        for (int kx = 0; kx < 3; ++kx) {
+          const bf8 b = tr_operand(xs + (ib * XPX + (y4 + i) * PW + kx) * 16 + tr);
 #pragma unroll
-        for (int m = 0; m < MB; ++m) from[(t * MB + m) * 64] = acc[t][m];
+          for (int ky = 0; ky < 3; ++ky) {
+            const int r = i - ky;
+            if (r < 0 || r >= 4) continue;
 #pragma unroll
-      for (int m = 0; m < MB; ++m) from[(9 * MB + m) * 64] = accb[m];
-    }
-    __syncthreads();
-    if (takes) {
+            for (int m = 0; m < MB; ++m)
+              acc[ky * 3 + kx][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r][m], b, acc[ky * 3 + kx][m], 0, 0, 0);
+          }
+        }
+      if (ib == 0)
 #pragma unroll
-      for (int t = 0; t < 9; ++t)
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int m = 0; m < MB; ++m) acc[t][m] += from[(t * MB + m) * 64];
-#pragma unroll
-      for (int m = 0; m < MB; ++m) accb[m] += from[(9 * MB + m) * 64];
+          for (int m = 0; m < MB; ++m)
+            accb[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[r][m], ones, accb[m], 0, 0, 0);
     }
   }
-  if (rq) return;
+  // the two row halves of each input channel half
+  f4* red = (f4*)lds + (size_t)ib * NACC * 64 + lane;
+  __syncthreads();
+  if (rh) {
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+#pragma unroll
+      for (int t = 0; t < 9; ++t) red[(t * MB + m) * 64] = acc[t][m];
+      red[(9 * MB + m) * 64] = accb[m];
+    }
+  }
+  __syncthreads();
+  if (rh) return;
+#pragma unroll
+  for (int m = 0; m < MB; ++m) {
+#pragma unroll
+    for (int t = 0; t < 9; ++t) acc[t][m] += red[(t * MB + m) * 64];
+    accb[m] += red[(9 * MB + m) * 64];
+  }
   // this workgroup's row of `part` (width values; dW, then db): lane (g, i16)
   // holds output channels 4 g .. + 3 of input channel i16
   float* row_out = part + (size_t)blockIdx.x * width;
@@ -1247,7 +1199,6 @@ extern "C" wv_status wv_cnn_get_params(wv_cnn* net, float* host_params, hipStrea
   return e == hipSuccess ? WV_OK : hip_fail(e, "wv_cnn_get_params");
 }
 
-static int conv_grid(int n, int h, int w) { return n * ((h + CH - 1) / CH) * ((w + CW - 1) / CW); }
 static int fwd_grid(int n, int h, int w) { return n * ((h + FH - 1) / FH) * ((w + FW - 1) / FW); }
 
 // The forward pass in one launch; keep: write the activations the backward
@@ -1314,7 +1265,6 @@ extern "C" wv_status wv_cnn_backward(wv_cnn* net, float* grads, hipStream_t s) {
   if (!net->grad_valid) return fail(WV_EINVAL, "wv_cnn_backward: no loss gradient");
   const int n = net->n, h = net->h, w = net->w;
   const Layer* L = net->layer;
-  const dim3 g(conv_grid(n, h, w)), b(256);
   // split over pixels: at most kWgradRows (kWgradRows0 for the first layer)
   // workgroups, each writing a row of partial sums that k_wsum adds up
   const int nb0 = n * ((h + BH - 1) / BH) * ((w + BW - 1) / BW), nb = n * ((h + GH - 1) / GH) * ((w + GW - 1) / GW);
@@ -1325,18 +1275,16 @@ extern "C" wv_status wv_cnn_backward(wv_cnn* net, float* grads, hipStream_t s) {
   float* rest = net->wpart + (size_t)rows0 * np0;
   auto part = [&](int l) { return rest + (L[l].w_off - np0); };
   // layer 4: dW4 from a3 and dz; d3 = (W4' * dz) masked by a3 > 0
-  hipLaunchKernelGGL((k_wgrad32<4>), gw, bw, 0, s, net->act[2], net->dz, part(3), npr, n, h, w, bpw);
-  hipLaunchKernelGGL((k_conv<4, HID>), g, b, 0, s, net->dz, net->wb[3], net->act[2], net->dbuf[0], n, h, w);
+  hipLaunchKernelGGL((k_back<4>), gw, bw, 0, s, net->act[2], net->dz, net->wb[3], net->dbuf[0], part(3), npr, n, h, w,
+                     bpw);
   // layer 3
-  hipLaunchKernelGGL((k_wgrad32<HID>), gw, bw, 0, s, net->act[1], net->dbuf[0], part(2), npr, n, h, w, bpw);
-  hipLaunchKernelGGL((k_conv<HID, HID>), g, b, 0, s, net->dbuf[0], net->wb[2], net->act[1], net->dbuf[1], n, h,
-                     w);
+  hipLaunchKernelGGL((k_back<HID>), gw, bw, 0, s, net->act[1], net->dbuf[0], net->wb[2], net->dbuf[1], part(2), npr, n,
+                     h, w, bpw);
   // layer 2
-  hipLaunchKernelGGL((k_wgrad32<HID>), gw, bw, 0, s, net->act[0], net->dbuf[1], part(1), npr, n, h, w, bpw);
-  hipLaunchKernelGGL((k_conv<HID, HID>), g, b, 0, s, net->dbuf[1], net->wb[1], net->act[0], net->dbuf[0], n, h,
-                     w);
+  hipLaunchKernelGGL((k_back<HID>), gw, bw, 0, s, net->act[0], net->dbuf[1], net->wb[1], net->dbuf[0], part(1), npr, n,
+                     h, w, bpw);
   // layer 1
-  hipLaunchKernelGGL(k_wgrad, dim3(rows0), b, 0, s, net->xin, net->dbuf[0], net->wpart, np0, n,
+  hipLaunchKernelGGL(k_wgrad, dim3(rows0), dim3(256), 0, s, net->xin, net->dbuf[0], net->wpart, np0, n,
                      h, w, bpw0);
   // every layer's rows into the gradient, and into the caller's copy
   hipLaunchKernelGGL(k_wsum, dim3((np + 63) / 64), dim3(512), 0, s, (const float*)net->wpart, rows0, np0,

@@ -1,7 +1,8 @@
 """The restoration network at the edges of its kernels' tiles: the forward
-pass's 14 x 26 output tile (one pixel, exactly one tile, one pixel more and
-less in each direction, several tiles), against the float64 oracle; the
-activations it keeps are checked through the gradients.
+pass's 14 x 26 output tile and the backward pass's 16 x 32 block (one pixel,
+exactly one tile, one pixel more and less in each direction, several tiles),
+against the float64 oracle; the activations it keeps are checked through the
+gradients.
 
 Tolerances: as in test_gpu_cnn, what differs is a bfloat16 rounding that flips
 (2^-8 relative) next to a boundary.  One flipped activation reaches up to 7 x 7
@@ -20,7 +21,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape", [(1, 1, 1), (1, 14, 26), (2, 13, 25), (1, 15, 27), (3, 28, 53), (1, 5, 80),
-                                   (1, 60, 3)])
+                                   (1, 60, 3), (1, 16, 32), (2, 17, 33), (1, 31, 63)])
 def test_forward_and_gradients_at_tile_edges(shape):
     from paper_2208_10859_amd import cnn
     x, t, params = _case(70 + shape[1], shape)
