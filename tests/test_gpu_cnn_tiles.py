@@ -48,3 +48,29 @@ def test_forward_and_gradients_at_tile_edges(shape):
     for k, (g, w) in enumerate(zip(cnn.unflatten(grads.cpu().numpy()), wg)):
         rel = np.linalg.norm(g - w) / max(np.linalg.norm(w), 1e-12)
         assert rel <= max(2e-4, 4 * 2.0 ** -8 / np.sqrt(32 * np.prod(shape))), (k, rel)
+
+
+def test_training_steps_leave_the_matrices_of_their_parameters():
+    """Adam rounds each parameter into the convolutions' matrices: after a few
+    steps the forward pass and the gradients are those of a new network given
+    the same parameters, bit for bit."""
+    from paper_2208_10859_amd import cnn
+    shape = (1, 20, 40)
+    x, t, params = _case(91, shape)
+    xd, td = _dev_x(x), _dev_t(t)
+    net, fresh = cnn.Net(800), cnn.Net(800)
+    net.set_params(cnn.flatten(params))
+    for s in range(1, 4):
+        net.train_step(xd, td, 1e-2, s)
+    got = net.get_params()
+    assert np.abs(got - cnn.flatten(params)).max() > 5e-3
+    fresh.set_params(got)
+    out = []
+    for k in (net, fresh):
+        z = torch.zeros(shape + (4,), dtype=torch.float32, device="cuda")
+        g = torch.zeros(cnn.param_count(), dtype=torch.float32, device="cuda")
+        k.forward(xd, z)
+        k.loss_grad(td)
+        k.backward(g)
+        out.append((z.cpu(), g.cpu()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
