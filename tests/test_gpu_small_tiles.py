@@ -109,3 +109,32 @@ def test_grey_calls_of_few_and_of_many_tiles():
         for r in res[1:]:
             for a, b in zip(r, res[0]):
                 assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("tile,n", [(16, 8), (16, 9), (16, 15), (16, 17), (16, 35), (16, 360), (16, 361), (16, 730),
+                                    (512, 9), (512, 13)])
+def test_mixed_level_counts_in_launches_of_any_size(tile, n):
+    """Tiles of different level counts are dealt over a launch: each is decoded
+    once and lands in its own slot (against the plain path, which takes them
+    in order)."""
+    from paper_2208_10859_amd import wv
+    levels = 3
+    mask = np.ones(n + 3, np.uint8)
+    mask[[1, 4, n]] = 0
+    lc = np.random.default_rng(n).integers(0, levels + 1, n + 3).astype(np.uint8)
+    res = []
+    for path in (wv.PATH_FUSED, wv.PATH_PLAIN):
+        dec = wv.Decoder((n + 3) * tile, tile, tile, levels, wv.W53, wv.YUV420)
+        dec.set_path(path)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(n)
+        coef = [[torch.randint(-40, 40, dec.plane_shape(p), generator=gen, device="cuda", dtype=torch.int16)
+                 for p in range(3)] for _ in range(3)]
+        ref = wv.Reference(dec)
+        outs = [torch.empty(dec.out_shape(n), dtype=torch.uint8, device="cuda") for _ in range(3)]
+        dec.decode_viewport(coef[0], 0, True, 3, mask, ref, outs[0], lc)
+        dec.decode_gop([(coef[1], False, 1), (coef[2], False, 2)], 1, mask, ref, outs[1:], lc)
+        torch.cuda.synchronize()
+        res.append(outs + list(ref.planes))
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
