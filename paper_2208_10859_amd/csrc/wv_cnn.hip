@@ -20,7 +20,6 @@ namespace cnn {
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 constexpr int HID = 32;
-constexpr int BH = 8, BW = 32;            // weight gradients: pixels per block, 8 rows x 32 columns
 
 // float -> bfloat16, round to nearest, ties to even (finite values)
 __device__ __forceinline__ uint16_t f2bf(float f) {
@@ -30,7 +29,6 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-constexpr int kpad16(int cin) { return (9 * cin + 15) / 16 * 16; }
 
 // Convolutions are implicit GEMMs on gfx950's v_mfma_f32_16x16x32_bf16: M =
 // output channels (16 per MFMA), N = pixels (16 consecutive columns of one
@@ -54,193 +52,13 @@ __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2v{a, b}, bf2));
 }
 
-// Weight and bias gradients of one layer: dW[o][tap][i] = sum over pixels of
-// dy[p][o] x[p + tap offset][i], as a GEMM with M = output channels, N = 9
-// taps x input channels (padded to 16), K = pixels, on
-// v_mfma_f32_16x16x32_bf16 (operands as above).  This kernel: the
-// first layer (image with 4 channels in memory, 3 real, dy with 32).  A
-// workgroup stages the transposed dy of an 8 x 32 block and three
-// column-shifted, channel-major copies of the input patch (so that four
-// consecutive pixels of an operand are one aligned 8-byte read), and loops
-// over `bpw` blocks.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad(const uint16_t* __restrict__ x,
-                                               const uint16_t* __restrict__ dy,
-                                               float* __restrict__ part, int width, int N, int H, int W,
-                                               int bpw) {
-  constexpr int CINM = 4, CINR = 3, COUTR = HID;
-  constexpr int KN = kpad16(CINM), MB = COUTR / 16, NB = KN / 16;
-  constexpr int NW = COUTR * 9 * CINR;     // weights of the layer; its COUTR biases follow
-  constexpr int PR = BH + 2;
-  // wave w computes the 16-column blocks nb = w, w + 4, ... of the result for
-  // every 16-channel block mb: one x operand read serves MB products
-  constexpr int PER_WAVE = (NB + 3) / 4;
-  // Row strides padded by 8 values: unpadded (512 and 640 bytes) the 16 rows
-  // of one operand read started on 1 or 2 distinct 16-byte bank groups (16-
-  // and 8-fold conflicts); 528 and 656 bytes spread them over all 16.
-  constexpr int DS = BH * BW + 8;          // dyt: one output channel
-  constexpr int XS = PR * BW + 8;          // xs: one (column shift, input channel) plane
-  __shared__ __align__(16) uint16_t dyt[COUTR * DS];
-  __shared__ __align__(16) uint16_t xs[3 * CINM * XS];
-  const int nbx = (W + BW - 1) / BW, nby = (H + BH - 1) / BH, nblocks = nbx * nby * N;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i16 = lane & 15, g4 = lane >> 4;
-  f4 acc[PER_WAVE][MB];
-#pragma unroll
-  for (int k = 0; k < PER_WAVE; ++k)
-#pragma unroll
-    for (int m = 0; m < MB; ++m) acc[k][m] = f4{0.f, 0.f, 0.f, 0.f};
-  // bias gradient: per-thread partial sums of the dy channels this thread
-  // loads (channels 8 (tid & 3) .. + 7)
-  float bpart[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) bpart[j] = 0.f;
-  // dy: 16-byte (8-channel) pixel pieces, zero outside the image, two
-  // horizontally adjacent pixels per item; x: the patch of the block grown by
-  // one pixel (34 columns), 8-byte pixels in pairs.
-  constexpr int DYI = BH * BW / 2 * 4, NDY = (DYI + 255) / 256;
-  constexpr int NPR = (BW + 2) / 2;          // column pairs per patch row
-  constexpr int XI = PR * NPR, NXI = (XI + 255) / 256;
-  uint4 dv[NDY][2];
-  uint2 xv[NXI][2];
-  // A block's global reads go into registers ahead of its turn, while the
-  // block before is multiplied: the staging waits for no memory.
-  auto load = [&](int blk) __attribute__((always_inline)) {
-    const int bx = blk % nbx, by = (blk / nbx) % nby, n = blk / (nbx * nby);
-#pragma unroll
-    for (int it = 0; it < NDY; ++it) {
-      const int idx = tid + 256 * it;
-      const int pp = idx >> 2, ch = idx & 3;
-      const int gy = by * BH + (2 * pp) / BW;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const int gx = bx * BW + (2 * pp) % BW + hh;
-        dv[it][hh] = make_uint4(0u, 0u, 0u, 0u);
-        if (idx < DYI && gy < H && gx < W)
-          dv[it][hh] = *(const uint4*)(dy + ((size_t)(n * H + gy) * W + gx) * 32 + ch * 8);
-      }
-    }
-#pragma unroll
-    for (int it = 0; it < NXI; ++it) {
-      const int idx = tid + 256 * it;
-      const int r = idx / NPR, m = idx - r * NPR;
-      const int gy = by * BH + r - 1;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh) {
-        const int gx = bx * BW + 2 * m + hh - 1;
-        xv[it][hh] = make_uint2(0u, 0u);
-        if (idx < XI && gy >= 0 && gy < H && gx >= 0 && gx < W)
-          xv[it][hh] = *(const uint2*)(x + ((size_t)(n * H + gy) * W + gx) * 4);
-      }
-    }
-  };
-  const int blk0 = blockIdx.x * bpw, blk1 = min(blk0 + bpw, nblocks);
-  load(blk0);
-  for (int blk = blk0; blk < blk1; ++blk) {
-    __syncthreads();   // the previous block's reads of dyt and xs are done
-    // dy transposed, dyt[o][r * 32 + c], a 4-byte word per pixel pair
-#pragma unroll
-    for (int it = 0; it < NDY; ++it) {
-      const int idx = tid + 256 * it;
-      if (idx >= DYI) break;
-      const int pp = idx >> 2, ch = idx & 3;
-      const uint32_t w0[4] = {dv[it][0].x, dv[it][0].y, dv[it][0].z, dv[it][0].w};
-      const uint32_t w1[4] = {dv[it][1].x, dv[it][1].y, dv[it][1].z, dv[it][1].w};
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint32_t h0 = (w0[j >> 1] >> (16 * (j & 1))) & 0xffffu;
-        const uint32_t h1 = (w1[j >> 1] >> (16 * (j & 1))) & 0xffffu;
-        *(uint32_t*)(dyt + (ch * 8 + j) * DS + 2 * pp) = h0 | (h1 << 16);
-        bpart[j] += bf2f((uint16_t)h0) + bf2f((uint16_t)h1);
-      }
-    }
-    // xs[kx][i][r][c] = x[by*8 + r - 1][bx*32 + c + kx - 1][i]: each pair of
-    // patch columns (2m, 2m + 1) goes to the copies whose column range holds
-    // it -- as one 4-byte word in copies 0 and 2 (columns 2m and 2m - 2 there,
-    // even), as two halves in copy 1
-#pragma unroll
-    for (int it = 0; it < NXI; ++it) {
-      const int idx = tid + 256 * it;
-      if (idx >= XI) break;
-      const int r = idx / NPR, m = idx - r * NPR;
-      const uint32_t w0[2] = {xv[it][0].x, xv[it][0].y};
-      const uint32_t w1[2] = {xv[it][1].x, xv[it][1].y};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t h0 = (w0[j >> 1] >> (16 * (j & 1))) & 0xffffu;
-        const uint32_t h1 = (w1[j >> 1] >> (16 * (j & 1))) & 0xffffu;
-        const int i = j, row = r * BW + 2 * m;
-        if (m < NPR - 1) {
-          *(uint32_t*)(xs + i * XS + row) = h0 | (h1 << 16);
-          xs[(CINM + i) * XS + row] = (uint16_t)h1;
-        }
-        if (m > 0) {
-          *(uint32_t*)(xs + (2 * CINM + i) * XS + row - 2) = h0 | (h1 << 16);
-          xs[(CINM + i) * XS + row - 1] = (uint16_t)h0;
-        }
-      }
-    }
-    __syncthreads();
-    if (blk + 1 < blk1) load(blk + 1);
-    // K steps of 32 pixels: one block row each, lane group g4 taking
-    // columns 8 g4 .. 8 g4 + 7 of both operands
-#pragma unroll 1
-    for (int row = 0; row < BH; ++row) {
-      const int c0 = g4 * 8;
-      // the dy operand of each 16-channel block, read once per row
-      bf8 a[MB];
-#pragma unroll
-      for (int m = 0; m < MB; ++m) a[m] = as_bf8(*(const uint4*)(dyt + (m * 16 + i16) * DS + row * BW + c0));
-#pragma unroll
-      for (int k = 0; k < PER_WAVE; ++k) {
-        const int nb = wave + 4 * k;
-        if (nb >= NB) break;
-        const int nn = nb * 16 + i16, tap = nn / CINM, i = nn - tap * CINM;
-        uint4 bx4 = make_uint4(0u, 0u, 0u, 0u);
-        if (tap < 9) {
-          const int ky = tap / 3, kx = tap - ky * 3;
-          bx4 = *(const uint4*)(xs + (kx * CINM + i) * XS + (row + ky) * BW + c0);
-        }
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-          acc[k][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], as_bf8(bx4), acc[k][m], 0, 0, 0);
-      }
-    }
-  }
-  // this workgroup's partial sums, plain stores into its row of `part` (rows
-  // of `width` values; parameter layout: dW, then db); k_wsum adds the rows up
-  float* row_out = part + (size_t)blockIdx.x * width;
-#pragma unroll
-  for (int k = 0; k < PER_WAVE; ++k) {
-    const int nb = wave + 4 * k;
-    if (nb >= NB) break;
-    const int nn = nb * 16 + i16, tap = nn / CINM, i = nn - tap * CINM;
-    if (tap >= 9 || i >= CINR) continue;
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int o = m * 16 + g4 * 4 + q;
-        if (o < COUTR) row_out[(o * 9 + tap) * CINR + i] = acc[k][m][q];
-      }
-  }
-  // bias gradient: lanes holding the same channels, then the four waves
-  __shared__ float bred[4][32];
-#pragma unroll
-  for (int j = 0; j < 8; ++j)
-#pragma unroll
-    for (int m = 4; m < 64; m <<= 1) bpart[j] += __shfl_xor(bpart[j], m);
-  if (lane < 4)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) bred[wave][lane * 8 + j] = bpart[j];
-  __syncthreads();
-  if (tid < COUTR) row_out[NW + tid] = bred[0][tid] + bred[1][tid] + bred[2][tid] + bred[3][tid];
-}
-
 // Backward pass of a layer with 32 input channels: its weight and bias
-// gradients (the same GEMM), and the gradient of its input dx (the convolution
-// of dy with the flipped, transposed kernel, masked by the ReLU that made the
-// input x: dx = bf16(x > 0 ? sum : 0)).  Both need the block of x and of dy with
-// a border, so one kernel stages them once; of its eight waves four compute
-// each, one of either kind on every SIMD.
+// gradients, dW[o][tap][i] = sum over pixels of dy[p][o] x[p + tap offset][i], as a
+// GEMM with M = output channels, N = taps x input channels, K = pixels; and the
+// gradient of its input dx (the convolution of dy with the flipped, transposed
+// kernel, masked by the ReLU that made the input x: dx = bf16(x > 0 ? sum : 0)).
+// Both need the block of x and of dy with a border, so one kernel stages them
+// once; of its eight waves four compute each, one of either kind on every SIMD.
 // A workgroup stages 16 x 32 pixel blocks, the next one's global reads under way
 // while one is multiplied.  The staged pixels stay as they are in memory,
 // [16-channel half][pixel][16].
@@ -255,45 +73,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // LDS at the end.
 // Data gradient: wave w takes rows 4 (w - 4) .. + 3, the whole weight matrix in
 // registers (18 operands of 8 bf16), loaded once.
+// FIRST (layer 2): dx is only needed for the first layer's weight gradient, so it
+// goes to LDS instead of memory, and the wave that computed it takes its products
+// with the image: four taps of a pixel's four channels are a transposing read's 16
+// columns.
 // What bounds it: the latency of its two rounds of global reads, then their
 // bytes (16 x 128 x 128, 32 dy channels: 50 MB, 9.6 us at a copy's rate).
 // There, 32 dy channels: 21 us; as two kernels 27.8 us (14.9 weights, 12.9
 // data), 3 dy channels: 14.2 us against 10.4 + 9.7.  With every wave doing both
-// parts in turn the registers ran out (23 and 14.9 us).  Weight gradients
+// parts in turn the registers ran out (23 and 14.9 us).  FIRST:
+// 25 us; with a kernel of its own for the first layer 20.8 + 7.5.  Weight gradients
 // from transposed copies written to LDS a word at a time took 19.4 us.
 //   DYC: dy channels in memory (32, or 4 of which 3 are real).
+//   img, part0, width0: FIRST: the image, rows of the first layer's sums.
 constexpr int GH = 16, GW = 32;           // block of pixels
 constexpr int GWAVES = 8;
 typedef short s4 __attribute__((ext_vector_type(4)));
 
+template <int PITCH = 16>   // values from pixel to pixel
 __device__ __forceinline__ bf8 tr_operand(const uint16_t* p) {
   using LP = __attribute__((address_space(3))) s4*;
   const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LP)(p));
-  const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LP)(p + 16 * 16));   // 16 pixels on
+  const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LP)(p + 16 * PITCH));   // 16 pixels on
   return as_bf8(__builtin_bit_cast(uint4, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7)));
 }
 
-template <int DYC>
+template <int DYC, bool FIRST>
 __global__ __launch_bounds__(64 * GWAVES) __attribute__((amdgpu_waves_per_eu(2)))
 void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, const uint16_t* __restrict__ wt,
-            uint16_t* __restrict__ dx, float* __restrict__ part, int width, int N, int H, int W, int bpw) {
+            uint16_t* __restrict__ dx, float* __restrict__ part, int width, const uint16_t* __restrict__ img,
+            float* __restrict__ part0, int width0, int N, int H, int W, int bpw) {
   constexpr int MB = DYC == 32 ? 2 : 1, COUTR = DYC == 32 ? 32 : 3, NW = COUTR * 9 * 32, NT = 64 * GWAVES;
   constexpr int PW = GW + 2, XPX = (GH + 2) * PW;               // staged pixels: the block and its border
   constexpr int NACC = 9 * MB + MB;                             // accumulator tiles of a wave
   constexpr int KP = kpad32(DYC), KS = KP / 32;                 // the data gradient's K steps
-  constexpr int STAGE = (2 + MB) * XPX * 16 * 2 + (DYC == 32 ? 0 : XPX * 8), REDUCE = 2 * NACC * 64 * 16;
+  constexpr bool IMG = DYC != 32 || FIRST;                      // a 4-channel image is staged too
+  constexpr int DXE = FIRST ? 2 * GH * GW * 16 : 0;             // the block's dx
+  constexpr int STAGE = ((2 + MB) * XPX * 16 + DXE) * 2 + (IMG ? XPX * 8 : 0);
+  constexpr int REDUCE = 2 * NACC * 64 * 16 + (FIRST ? 3 * 8 * 64 * 16 : 0);
   __shared__ __align__(16) unsigned char lds[STAGE > REDUCE ? STAGE : REDUCE];
   uint16_t* xs = (uint16_t*)lds;               // [2][XPX][16]
   uint16_t* ds = xs + 2 * XPX * 16;            // [MB][XPX][16]
-  uint2* d4 = (uint2*)(ds + MB * XPX * 16);    // DYC = 4: [XPX][4]
+  uint16_t* dxs = ds + MB * XPX * 16;          // FIRST: [2][GH * GW][16]
+  uint2* im4 = (uint2*)(dxs + DXE);            // dy (DYC = 4) or the image (FIRST): [XPX][4]
   const int nbx = (W + GW - 1) / GW, nby = (H + GH - 1) / GH, nblocks = nbx * nby * N;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int i16 = lane & 15, g = lane >> 4;
   // this lane's part of an operand's first 16 pixels
   const int tr = (4 * g + (i16 >> 2)) * 16 + 4 * (i16 & 3);
 
-  constexpr int NX = (XPX * 4 + NT - 1) / NT, ND = DYC == 32 ? NX : (XPX + NT - 1) / NT;
-  uint4 xv[NX], dv[ND];
+  constexpr int NX = (XPX * 4 + NT - 1) / NT, NI = (XPX + NT - 1) / NT;
+  uint4 xv[NX], dv[DYC == 32 ? NX : 1];
+  uint2 iv[IMG ? NI : 1];
+  const uint16_t* __restrict__ src4 = FIRST ? img : dy;
   auto load = [&](int blk) __attribute__((always_inline)) {
     const int bx = blk % nbx, by = (blk / nbx) % nby, n = blk / (nbx * nby);
 #pragma unroll
@@ -308,16 +140,14 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
         if constexpr (DYC == 32) dv[it] = *(const uint4*)(dy + e);
       }
     }
-    if constexpr (DYC != 32) {
+    if constexpr (IMG) {
 #pragma unroll
-      for (int it = 0; it < ND; ++it) {
+      for (int it = 0; it < NI; ++it) {
         const int px = tid + NT * it, r = px / PW, c = px - r * PW;
         const int gy = by * GH + r - 1, gx = bx * GW + c - 1;
-        dv[it] = make_uint4(0u, 0u, 0u, 0u);
-        if (px < XPX && gy >= 0 && gy < H && gx >= 0 && gx < W) {
-          const uint2 v = *(const uint2*)(dy + ((size_t)(n * H + gy) * W + gx) * 4);
-          dv[it] = make_uint4(v.x, v.y, 0u, 0u);
-        }
+        iv[it] = make_uint2(0u, 0u);
+        if (px < XPX && gy >= 0 && gy < H && gx >= 0 && gx < W)
+          iv[it] = *(const uint2*)(src4 + ((size_t)(n * H + gy) * W + gx) * 4);
       }
     }
   };
@@ -334,14 +164,16 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
         if constexpr (DYC == 32) *(uint4*)(ds + at) = dv[it];
       }
     }
-    if constexpr (DYC != 32) {
+    if constexpr (IMG) {
 #pragma unroll
-      for (int it = 0; it < ND; ++it) {
+      for (int it = 0; it < NI; ++it) {
         const int px = tid + NT * it;
         if (px < XPX) {
-          d4[px] = make_uint2(dv[it].x, dv[it].y);
-          *(uint4*)(ds + px * 16) = make_uint4(dv[it].x, dv[it].y & 0xffffu, 0u, 0u);   // three real channels
-          *(uint4*)(ds + px * 16 + 8) = make_uint4(0u, 0u, 0u, 0u);
+          im4[px] = iv[it];
+          if constexpr (DYC != 32) {
+            *(uint4*)(ds + px * 16) = make_uint4(iv[it].x, iv[it].y & 0xffffu, 0u, 0u);   // three real channels
+            *(uint4*)(ds + px * 16 + 8) = make_uint4(0u, 0u, 0u, 0u);
+          }
         }
       }
     }
@@ -349,6 +181,8 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
     if (blk + 1 < blk1) load(blk + 1);
   };
   load(blk0);
+  const uint32_t one2 = 0x3f803f80u;
+  const bf8 ones = as_bf8(make_uint4(one2, one2, one2, one2));
   // The waves' parts have loops of their own (with one loop both parts' registers
   // would be held); their barriers pair up.
   if (wave >= 4) {
@@ -359,6 +193,23 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
     for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
       for (int nb = 0; nb < 2; ++nb) wr[ks][nb] = as_bf8(*(const uint4*)(wt + (nb * 16 + i16) * KP + ks * 32 + 8 * g));
+    // FIRST: the first layer's weight gradient of this wave's rows: 9 taps x 4
+    // image channels as three column blocks of four taps; the bias by ones
+    f4 acc1[2][3], accb1[2];
+    const uint16_t* ip[3];   // this lane's part of the three operands, first row
+    if constexpr (FIRST) {
+#pragma unroll
+      for (int nb = 0; nb < 3; ++nb) {
+        const int tap = min(nb * 4 + (i16 & 3), 8);
+        ip[nb] = (const uint16_t*)(im4 + (cr + tap / 3) * PW + tap % 3 + 4 * g + (i16 >> 2));
+      }
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        accb1[m] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int nb = 0; nb < 3; ++nb) acc1[m][nb] = f4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
     for (int blk = blk0; blk < blk1; ++blk) {
       stage(blk);
       // this wave's four rows, 16 columns at a time
@@ -395,7 +246,7 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               // taps t0 = 8 ks + 2 g and t0 + 1, four channels each; taps >= 9 are zero
-              const uint2* p8 = d4 + p0 + r * PW;
+              const uint2* p8 = im4 + p0 + r * PW;
               const int t0 = ks * 8 + 2 * g, t1 = t0 + 1;
               const int u0 = min(t0, 8), u1 = min(t1, 8);
               uint2 lo = p8[(u0 / 3) * PW + u0 % 3];
@@ -414,7 +265,7 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int gy = by * GH + cr + r;
-          if (gy >= H || gx >= W) continue;
+          if (!FIRST && (gy >= H || gx >= W)) continue;   // FIRST: zeros there (the mask's)
           const size_t px = (size_t)(n * H + gy) * W + gx;
 #pragma unroll
           for (int nb = 0; nb < 2; ++nb) {
@@ -423,13 +274,63 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
             float v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[q] = bf2f(mh[q]) > 0.f ? o[r][nb][q] : 0.f;
-            *(uint2*)(dx + px * 32 + nb * 16 + 4 * g) = make_uint2(pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3]));
+            const uint2 pk = make_uint2(pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3]));
+            if constexpr (FIRST)
+              *(uint2*)(dxs + (nb * GH * GW + (cr + r) * GW + cb * 16 + i16) * 16 + 4 * g) = pk;
+            else
+              *(uint2*)(dx + px * 32 + nb * 16 + 4 * g) = pk;
+          }
+        }
+      }
+      if constexpr (FIRST) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          bf8 a[2];
+#pragma unroll
+          for (int m = 0; m < 2; ++m) a[m] = tr_operand(dxs + (m * GH * GW + (cr + r) * GW) * 16 + tr);
+#pragma unroll
+          for (int nb = 0; nb < 3; ++nb) {
+            const bf8 b = tr_operand<4>(ip[nb] + r * PW * 4);
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+              acc1[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], b, acc1[m][nb], 0, 0, 0);
+          }
+#pragma unroll
+          for (int m = 0; m < 2; ++m) accb1[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m], ones, accb1[m], 0, 0, 0);
+        }
+      }
+    }
+    // FIRST: the four waves' sums, after the weight waves' part of the buffer
+    f4* red1 = (f4*)lds + 2 * NACC * 64 + lane;
+    __syncthreads();
+    if (FIRST && wave > 4) {
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+#pragma unroll
+        for (int nb = 0; nb < 3; ++nb) red1[((wave - 5) * 8 + m * 4 + nb) * 64] = acc1[m][nb];
+        red1[((wave - 5) * 8 + m * 4 + 3) * 64] = accb1[m];
+      }
+    }
+    __syncthreads();
+    if (FIRST && wave == 4) {
+      float* row0 = part0 + (size_t)blockIdx.x * width0;
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+          f4 v = nb < 3 ? acc1[m][nb < 3 ? nb : 0] : accb1[m];
+#pragma unroll
+          for (int k = 0; k < 3; ++k) v += red1[(k * 8 + m * 4 + nb) * 64];
+          const int tap = nb * 4 + (i16 >> 2), i = i16 & 3;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int o = m * 16 + 4 * g + q;
+            if (nb < 3 && tap < 9 && i < 3) row0[(o * 9 + tap) * 3 + i] = v[q];
+            if (nb == 3 && i16 == 0) row0[HID * 27 + o] = v[q];
           }
         }
       }
     }
-    __syncthreads();
-    __syncthreads();
     return;
   }
   // weight gradient
@@ -441,8 +342,6 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t][m] = f4{0.f, 0.f, 0.f, 0.f};
   }
-  const uint32_t one2 = 0x3f803f80u;
-  const bf8 ones = as_bf8(make_uint4(one2, one2, one2, one2));
   for (int blk = blk0; blk < blk1; ++blk) {
     stage(blk);
     // eight rows of the block, four at a time
@@ -515,19 +414,19 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
 // and writes the gradient (and the caller's copy) in a fixed order.
 // What bounds it: the rows' bytes.  One launch per
 // layer with atomics into a cleared gradient, and a copy of it, took
-// 4 x 4.5 + 8 us of a 16 x 128 x 128 step; this one takes 7 us (22 MB).
-// part: rows0 rows of the `first` parameters of the first layer, then (from
-// `rest` on) `rows` rows of the others.
-__global__ __launch_bounds__(512) void k_wsum(const float* __restrict__ part, int rows0, int first,
+// 4 x 4.5 + 8 us of a 16 x 128 x 128 step; this one takes 6.2 us (20 MB).
+// part: `rows` rows of the `first` parameters of the first layer, then (from
+// `rest` on) of the others.
+__global__ __launch_bounds__(512) void k_wsum(const float* __restrict__ part, int first,
                                               const float* __restrict__ rest, int rows, int width, float* __restrict__ g, float* __restrict__ g2) {
   __shared__ float red[8][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.x * 64 + lane;
   float s = 0.f;
   if (j < width) {
-    const int n = j < first ? rows0 : rows, stride = j < first ? first : width - first;
+    const int stride = j < first ? first : width - first;
     const float* p = j < first ? part + j : rest + (j - first);
 #pragma unroll 8
-    for (int r = wave; r < n; r += 8) s += p[(size_t)r * stride];
+    for (int r = wave; r < rows; r += 8) s += p[(size_t)r * stride];
   }
   red[wave][lane] = s;
   __syncthreads();
@@ -1059,7 +958,7 @@ using wvp::hip_fail;
 
 // weight gradients: at most this many workgroups (the first layer's kernel runs
 // two per CU, the others' one), each writing one row of partial sums
-constexpr int kWgradRows0 = 512, kWgradRows = 256;
+constexpr int kWgradRows = 256;
 
 constexpr int kMaxGuardTiles = 65536;
 
@@ -1163,12 +1062,10 @@ extern "C" wv_status wv_cnn_create(wv_cnn** out, int64_t max_pixels) {
   alloc((void**)&net->guard_part, (P / 2048 + kMaxGuardTiles) * sizeof(GuardPart));
   alloc((void**)&net->guard_use, (kMaxGuardTiles + 1) * sizeof(int));
   alloc((void**)&net->crops, 3 * 4096 * sizeof(int));
-  // a weight-gradient workgroup has at least one pixel; every row is written
-  // before it is read
-  const size_t np0 = net->layer[1].w_off, npr = net->n_params - np0;
+  // a backward workgroup has at least one pixel; every row is written before it
+  // is read
   if (e == hipSuccess)
-    e = hipMalloc((void**)&net->wpart, (std::min<size_t>(kWgradRows0, P) * np0 + std::min<size_t>(kWgradRows, P) * npr) *
-                                           sizeof(float));
+    e = hipMalloc((void**)&net->wpart, std::min<size_t>(kWgradRows, P) * net->n_params * sizeof(float));
   if (e != hipSuccess) {
     wv_cnn_destroy(net);
     return e == hipErrorOutOfMemory ? fail(WV_ENOMEM, "wv_cnn buffers: %s", hipGetErrorString(e))
@@ -1293,29 +1190,25 @@ extern "C" wv_status wv_cnn_backward(wv_cnn* net, float* grads, hipStream_t s) {
   if (!net->grad_valid) return fail(WV_EINVAL, "wv_cnn_backward: no loss gradient");
   const int n = net->n, h = net->h, w = net->w;
   const Layer* L = net->layer;
-  // split over pixels: at most kWgradRows (kWgradRows0 for the first layer)
-  // workgroups, each writing a row of partial sums that k_wsum adds up
-  const int nb0 = n * ((h + BH - 1) / BH) * ((w + BW - 1) / BW), nb = n * ((h + GH - 1) / GH) * ((w + GW - 1) / GW);
-  const int bpw0 = (nb0 + kWgradRows0 - 1) / kWgradRows0, bpw = (nb + kWgradRows - 1) / kWgradRows;
-  const int rows0 = (nb0 + bpw0 - 1) / bpw0, rows = (nb + bpw - 1) / bpw;
+  // split over pixels: at most kWgradRows workgroups, each writing a row of
+  // partial sums that k_wsum adds up
+  const int nb = n * ((h + GH - 1) / GH) * ((w + GW - 1) / GW), bpw = (nb + kWgradRows - 1) / kWgradRows;
+  const int rows = (nb + bpw - 1) / bpw;
   const dim3 gw(rows), bw(64 * GWAVES);
   const int np = net->n_params, np0 = L[1].w_off, npr = np - np0;   // parameters of the first layer, of the others
-  float* rest = net->wpart + (size_t)rows0 * np0;
+  float* rest = net->wpart + (size_t)rows * np0;
   auto part = [&](int l) { return rest + (L[l].w_off - np0); };
   // layer 4: dW4 from a3 and dz; d3 = (W4' * dz) masked by a3 > 0
-  hipLaunchKernelGGL((k_back<4>), gw, bw, 0, s, net->act[2], net->dz, net->wb[3], net->dbuf[0], part(3), npr, n, h, w,
-                     bpw);
+  hipLaunchKernelGGL((k_back<4, false>), gw, bw, 0, s, net->act[2], net->dz, net->wb[3], net->dbuf[0], part(3), npr,
+                     nullptr, nullptr, 0, n, h, w, bpw);
   // layer 3
-  hipLaunchKernelGGL((k_back<HID>), gw, bw, 0, s, net->act[1], net->dbuf[0], net->wb[2], net->dbuf[1], part(2), npr, n,
-                     h, w, bpw);
-  // layer 2
-  hipLaunchKernelGGL((k_back<HID>), gw, bw, 0, s, net->act[0], net->dbuf[1], net->wb[1], net->dbuf[0], part(1), npr, n,
-                     h, w, bpw);
-  // layer 1
-  hipLaunchKernelGGL(k_wgrad, dim3(rows0), dim3(256), 0, s, net->xin, net->dbuf[0], net->wpart, np0, n,
-                     h, w, bpw0);
+  hipLaunchKernelGGL((k_back<HID, false>), gw, bw, 0, s, net->act[1], net->dbuf[0], net->wb[2], net->dbuf[1], part(2),
+                     npr, nullptr, nullptr, 0, n, h, w, bpw);
+  // layer 2, and the weights of layer 1 from the d1 it computes
+  hipLaunchKernelGGL((k_back<HID, true>), gw, bw, 0, s, net->act[0], net->dbuf[1], net->wb[1], nullptr, part(1), npr,
+                     net->xin, net->wpart, np0, n, h, w, bpw);
   // every layer's rows into the gradient, and into the caller's copy
-  hipLaunchKernelGGL(k_wsum, dim3((np + 63) / 64), dim3(512), 0, s, (const float*)net->wpart, rows0, np0,
+  hipLaunchKernelGGL(k_wsum, dim3((np + 63) / 64), dim3(512), 0, s, (const float*)net->wpart, np0,
                      (const float*)rest, rows, np, net->grads,
                      grads == net->grads ? nullptr : grads);
   const hipError_t e = hipGetLastError();
