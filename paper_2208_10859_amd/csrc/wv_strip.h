@@ -1189,7 +1189,10 @@ __device__ __forceinline__ std::conditional_t<SET, SetSrc<CT>, const WV_G CT*> p
     const Job& job, int p, size_t tile_off, size_t band_elems) {
   const WV_G CT* b = uniform((const WV_G CT*)job.coef[p] + tile_off);
   if constexpr (SET)
-    return SetSrc<CT>{b, b + band_elems, b + (size_t)job.hband * band_elems, job.qstep, job.hq[0],
+    // scalar pointers: left to itself the compiler kept two of the three in
+    // vector registers, and every load took a 64-bit vector address of its own
+    // (VALU instructions of the 5/3 set kernel 4290 -> 4062; sets 2 to 4 % faster)
+    return SetSrc<CT>{b, uniform(b + band_elems), uniform(b + (size_t)job.hband * band_elems), job.qstep, job.hq[0],
                       job.hq[1]};
   else
     return b;
