@@ -1238,12 +1238,15 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
   py.win[0] = sm.ya();
   py.win[1] = sm.yb;
   cone<LF, L>(st * R, R, P, py.a, py.b);
-  // Phased schedule: both chroma planes, each with code of its own (a phase's
-  // waves may take either).  Chain schedule: waves 1 and 2 take one plane each
-  // through the same code; with a copy per plane the 9/7 kernel was 91 KB, more
-  // than the instruction cache holds; shared 64 KB (GOPs 1 to 2 % faster).
-  constexpr int NPC = SCHED == 1 ? 1 : 2;
-  const int cp = SCHED == 1 ? (wave == 2) : 0;   // the plane of pc[0]
+  // Chain schedule: waves 1 and 2 take one chroma plane each.  SHARE: through
+  // the same code (the plane is a uniform index); with a copy per plane the 9/7
+  // kernel was 91 KB, more than the instruction cache holds, shared 64 KB (GOPs
+  // 1 to 2 % faster, sets 1 %), and 5/3 tiles of 256 took 80 instead of 78 us a
+  // GOP.  The 5/3 kernel of stored 512-sample tiles is better with a copy per
+  // plane, whose LDS addresses are constants (frames 71.5 -> 70.4 us, GOPs 0 to 1 %).
+  constexpr bool SHARE = SCHED == 1 && (SET || std::is_same<LF, Inv97>::value || P < 512);
+  constexpr int NPC = SHARE ? 1 : 2;
+  const int cp = SHARE ? (wave == 2) : 0;   // the plane of pc[0]
   Plane<LF, L, SrcT> pc[NPC];
   if constexpr (YUV) {
 #pragma unroll
@@ -1306,11 +1309,10 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
       else
         seg_run<LF, P, P, K1, L == 1, false>(ly, qs, sw, sa, srows, lane, j0y, lout);
     };
-    // the finest rows of this wave's chroma plane
-    auto chroma1 = [&]() __attribute__((always_inline)) {
+    // the finest rows of chroma plane p
+    auto chroma1 = [&](const Plane<LF, L, SrcT>& pl, int p) __attribute__((always_inline)) {
       constexpr int KC = chroma_pairs<PC, RC>(), C = RL<PC>::C;
-      const Plane<LF, L, SrcT>& pl = pc[0];
-      RT* chr = sm.chr[YUV ? cp : 0];
+      RT* chr = sm.chr[YUV ? p : 0];
       level<LF, PC, L, 1, KC>(pl, qs, lc, 0, 1, lane, [&](int g, int j0, int) {
         ChromaOut<LF, PC, C, !SET> e;
         e.ref = pl.ref;
@@ -1340,7 +1342,9 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
       if (wave == 0) chain<LF, P, L, 3, R>(py, qs, lc, lane);
     }
     if constexpr (YUV && L >= 2) {
-      if (cwave) chain<LF, PC, L, 2, RC>(pc[0], qs, lc, lane);
+      static_for<0, NPC>([&](auto K) {
+        if (SHARE ? cwave : wave == 1 + K) chain<LF, PC, L, 2, RC>(pc[K], qs, lc, lane);
+      });
     }
     if constexpr (phase_a) lds_barrier();
     __builtin_amdgcn_s_setprio(1);
@@ -1354,7 +1358,9 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
         }
       }
       if constexpr (YUV) {
-        if (cwave) chroma1();
+        static_for<0, NPC>([&](auto K) {
+          if (SHARE ? cwave : wave == 1 + K) chroma1(pc[K], cp + K);
+        });
       }
       lds_barrier();
     }
