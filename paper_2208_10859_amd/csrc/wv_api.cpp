@@ -591,7 +591,10 @@ extern "C" wv_status wv_encode_intra(wv_ctx* c, const void* const* src, void* co
   *c->enc_flag = 0;
   hipError_t e = launch_encode(c->d.wavelet, c->nplanes, c->n_tiles, c->d.tile, c->d.levels, qstep, src,
                                coeffs, c->enc_ws, c->enc_flag, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  // also after a failed launch: the kernels before it write the caller's planes
+  // and the workspace, which the next call uses
+  const hipError_t done = hipStreamSynchronize(s);
+  if (e == hipSuccess) e = done;
   if (e != hipSuccess) return hip_fail(e, "wv_encode_intra");
   if (*(volatile int*)c->enc_flag) return fail(WV_EINVAL, "a quantisation index falls outside int16 (raise qstep)");
   return WV_OK;

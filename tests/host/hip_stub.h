@@ -1,0 +1,56 @@
+// A HIP runtime that only counts: the host sources of libwv compile against it
+// with a plain C++ compiler, so that their bookkeeping runs without a device.
+// "Device" memory is host memory; work is enqueued by the test's own launchers.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+#include <cstdlib>
+#include <cstring>
+
+namespace stub {
+inline std::atomic<int> live_device{0}, live_host{0};   // allocations not yet freed
+inline hipError_t (*stream_sync)(hipStream_t) = nullptr;
+}  // namespace stub
+
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) {
+  *p = std::malloc(n);
+  ++stub::live_device;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  if (p) --stub::live_device;
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = std::calloc(1, n);
+  ++stub::live_host;
+  return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+  if (p) --stub::live_host;
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipMemset(void* p, int v, size_t n) { std::memset(p, v, n); return hipSuccess; }
+hipError_t hipMemsetAsync(void* p, int v, size_t n, hipStream_t) { return hipMemset(p, v, n); }
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) {
+  std::memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) { return stub::stream_sync ? stub::stream_sync(s) : hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = nullptr; return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* t, hipEvent_t, hipEvent_t) { *t = 0.f; return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "stub"; }
+}

@@ -1,0 +1,31 @@
+"""The library's host sources compiled with a plain C++ compiler against a
+runtime that only counts (tests/host): bookkeeping that a device would hide or
+that must not go wrong on one.  Host-only: no device is touched."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HOST = os.path.join(ROOT, "tests", "host")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+def _run(name, tmp_path, *args):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no C++ compiler")
+    exe = str(tmp_path / name)
+    subprocess.run([cxx, "-std=c++17", "-O1", "-w", "-pthread", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include",
+                    f"-I{ROOT}/include", f"-I{ROOT}/paper_2208_10859_amd/csrc", f"-I{HOST}",
+                    os.path.join(HOST, name + ".cpp"), "-o", exe], check=True, timeout=300)
+    r = subprocess.run([exe, *args], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+    return r.stdout
+
+
+def test_encoder_call_waits_for_its_kernels_also_after_an_error(tmp_path):
+    """The encoder's kernels write the caller's planes and a workspace that
+    outlives the call: no call may return while one of them runs."""
+    _run("encode_calls", tmp_path)
