@@ -13,6 +13,7 @@
 
 #include "wv_cnn.h"
 #include "wv_ctx.h"
+#include "wv_dev.h"
 
 namespace wv {
 namespace cnn {
@@ -283,6 +284,7 @@ void k_back(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, con
         }
       }
       if constexpr (FIRST) {
+        wave_lds_sync();   // the transposing reads take pixels that other lanes wrote
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           bf8 a[2];

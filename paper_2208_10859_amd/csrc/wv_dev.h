@@ -117,5 +117,13 @@ __device__ __forceinline__ int xcd_remap(int b, int g) {
   return x * q + min(x, r) + i;
 }
 
+// Ordering of one wave's LDS writes before its own later reads (DS
+// instructions of a wave execute in order; this only keeps the compiler from
+// moving them).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 
 }  // namespace wv

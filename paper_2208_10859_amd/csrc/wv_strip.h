@@ -1156,15 +1156,6 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Ordering of one wave's LDS writes before its own later reads (DS
-// instructions of a wave execute in order; this only keeps the compiler from
-// moving them).
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-}
-
 // The coarse levels L .. LAST of a plane as a chain on one wave (strips of ROWS
 // rows).  (Loading the first segments of every level before the first is
 // computed was slower: 8 to 15 % for 9/7 GOPs.)

@@ -74,3 +74,25 @@ def test_training_steps_leave_the_matrices_of_their_parameters():
         k.backward(g)
         out.append((z.cpu(), g.cpu()))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("shape", [(1, 289, 449), (601, 5, 7)])
+def test_gradients_of_several_blocks_per_workgroup(shape):
+    """More than 256 blocks: a workgroup of the backward kernel takes two (285
+    blocks) or three (601) in turn, the last one of them a single block, and hands
+    each block's first-layer signals over in LDS once more; the first shape has
+    more pixels than the loss kernel takes in one stride.  test_gpu_cnn's
+    tolerances."""
+    from paper_2208_10859_amd import cnn
+    x, t, params = _case(17 + shape[0], shape)
+    net = cnn.Net(int(np.prod(shape)))
+    net.set_params(cnn.flatten(params))
+    net.forward(_dev_x(x))
+    loss = net.loss_grad(_dev_t(t))
+    grads = torch.full((cnn.param_count(),), 3.0, dtype=torch.float32, device="cuda")
+    net.backward(grads)
+    want_loss, wg = ocnn.loss_and_grads(x, t, params, round_acts=True)
+    assert abs(loss.item() - want_loss) <= 1e-5 * want_loss
+    for k, (g, w) in enumerate(zip(cnn.unflatten(grads.cpu().numpy()), wg)):
+        rel = np.linalg.norm(g - w) / max(np.linalg.norm(w), 1e-12)
+        assert rel <= 2e-4, (k, rel)
