@@ -255,10 +255,10 @@ wv_status wv_foveation_levels(const wv_desc* desc, double yaw, double pitch, dou
  * level -- and the uniform quantiser q = sign(c) floor(|c|/qstep + 1/2)).
  * src: device tile-major uint8 planes; coeffs: device tile-major planes,
  * int16 indices (5/3) or float32 values qstep*q (9/7, computed in float64).
- * Synchronises the stream.  The first call of a context with tiles of 256 or
- * 512 samples and more than two levels allocates a workspace (at most half a
- * byte per sample for 5/3, one for 9/7) that the context keeps; calls of
- * several threads on one context take turns.
+ * Synchronises the stream.  With tiles of 256 or 512 samples and more than two
+ * levels a call needs a workspace (at most half a byte per sample for 5/3, one
+ * for 9/7): the context keeps one for each of up to four calls that threads
+ * have made at the same time; calls beyond four allocate and free their own.
  * Errors: WV_EINVAL (NULL planes, qstep < 1, an index outside int16),
  * WV_ENOMEM, WV_EDEVICE. */
 wv_status wv_encode_intra(wv_ctx* ctx, const void* const* src, void* const* coeffs,

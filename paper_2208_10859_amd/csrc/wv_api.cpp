@@ -94,10 +94,10 @@ wv_status wv_create(wv_ctx** out, const wv_desc* desc) {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, c->device);
   if (e == hipSuccess) e = hipMalloc((void**)&c->counter, 2 * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->counter, 0, 2 * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipHostMalloc((void**)&c->tab_host, kTableSlots * kTableBytes + sizeof(int), hipHostMallocDefault);
-  if (e == hipSuccess) {
-    c->enc_flag = (int*)(c->tab_host + kTableSlots * kTableBytes);
-  }
+  if (e == hipSuccess) e = hipHostMalloc((void**)&c->tab_host, kTableSlots * kTableBytes + kEncSlots * sizeof(int),
+                                         hipHostMallocDefault);
+  for (; e == hipSuccess && c->enc_n < kEncSlots; ++c->enc_n)
+    c->enc_idle[c->enc_n].flag = (int*)(c->tab_host + kTableSlots * kTableBytes) + c->enc_n;
   if (e == hipSuccess) e = hipMalloc((void**)&c->tab_dev, kTableSlots * kTableBytes);
   for (int i = 0; e == hipSuccess && i < kTableSlots; ++i)
     e = hipEventCreateWithFlags(&c->tab_done[i], hipEventDisableTiming);
@@ -124,7 +124,8 @@ wv_status wv_destroy(wv_ctx* c) {
   hipDeviceSynchronize();
   if (c->counter) hipFree(c->counter);
   if (c->plain_ws) hipFree(c->plain_ws);
-  if (c->enc_ws) hipFree(c->enc_ws);
+  for (const EncSlot& slot : c->enc_idle)
+    if (slot.ws) hipFree(slot.ws);
   if (c->tab_dev) hipFree(c->tab_dev);
   if (c->tab_host) hipHostFree(c->tab_host);
   for (int i = 0; i < kTableSlots; ++i)
@@ -572,6 +573,27 @@ extern "C" wv_status wv_decode_batch(int32_t n_jobs, const wv_job* jobs, hipStre
 }
 
 // ---------------------------------------------------------------- encoder
+// An encoder call's slot: an idle one of the context, else the call's own.
+struct EncTurn {
+  wv_ctx* c;
+  EncSlot slot;
+  bool own;
+  explicit EncTurn(wv_ctx* ctx) : c(ctx) {
+    std::lock_guard<std::mutex> lock(c->enc_mu);
+    own = c->enc_n == 0;
+    if (!own) slot = c->enc_idle[--c->enc_n];   // the last one used: it has a workspace
+  }
+  ~EncTurn() {
+    if (own) {
+      if (slot.ws) hipFree(slot.ws);
+      if (slot.flag) hipHostFree(slot.flag);
+      return;
+    }
+    std::lock_guard<std::mutex> lock(c->enc_mu);
+    c->enc_idle[c->enc_n++] = slot;
+  }
+};
+
 extern "C" wv_status wv_encode_intra(wv_ctx* c, const void* const* src, void* const* coeffs,
                                      int32_t qstep, hipStream_t s) {
   g_err[0] = 0;
@@ -580,23 +602,28 @@ extern "C" wv_status wv_encode_intra(wv_ctx* c, const void* const* src, void* co
   for (int p = 0; p < c->nplanes; ++p)
     if (!src[p] || !coeffs[p]) return fail(WV_EINVAL, "plane %d pointer is NULL", p);
   const size_t bytes = encode_workspace_bytes(c->d.wavelet, c->nplanes, c->n_tiles, c->d.tile, c->d.levels);
-  std::lock_guard<std::mutex> lock(c->enc_mu);
-  if (bytes && !c->enc_ws) {
-    const hipError_t e = hipMalloc(&c->enc_ws, bytes);
+  EncTurn turn(c);
+  EncSlot& slot = turn.slot;
+  if (!slot.flag && hipHostMalloc((void**)&slot.flag, sizeof(int), hipHostMallocDefault) != hipSuccess) {
+    slot.flag = nullptr;
+    return fail(WV_ENOMEM, "encoder flag");
+  }
+  if (bytes && !slot.ws) {
+    const hipError_t e = hipMalloc(&slot.ws, bytes);
     if (e != hipSuccess) {
-      c->enc_ws = nullptr;
+      slot.ws = nullptr;
       return fail(WV_ENOMEM, "encoder workspace: %s", hipGetErrorString(e));
     }
   }
-  *c->enc_flag = 0;
+  *slot.flag = 0;
   hipError_t e = launch_encode(c->d.wavelet, c->nplanes, c->n_tiles, c->d.tile, c->d.levels, qstep, src,
-                               coeffs, c->enc_ws, c->enc_flag, s);
+                               coeffs, slot.ws, slot.flag, s);
   // also after a failed launch: the kernels before it write the caller's planes
-  // and the workspace, which the next call uses
+  // and the slot's workspace, which the next call uses
   const hipError_t done = hipStreamSynchronize(s);
   if (e == hipSuccess) e = done;
   if (e != hipSuccess) return hip_fail(e, "wv_encode_intra");
-  if (*(volatile int*)c->enc_flag) return fail(WV_EINVAL, "a quantisation index falls outside int16 (raise qstep)");
+  if (*(volatile int*)slot.flag) return fail(WV_EINVAL, "a quantisation index falls outside int16 (raise qstep)");
   return WV_OK;
 }
 

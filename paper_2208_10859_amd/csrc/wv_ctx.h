@@ -26,6 +26,14 @@ inline size_t coeff_bytes(const wv_desc& d) { return d.wavelet == WV_W53 ? 2 : 4
 inline size_t sample_bytes(const wv_desc& d) { return d.wavelet == WV_W53 ? 1 : 4; }
 bool variant_fits(const wv_desc& d, const wv::Variant* v);
 
+// A process' streams share four hardware queues: more encoder calls than that do
+// not overlap on the device, and need not be served without an allocation.
+constexpr int kEncSlots = 4;
+struct EncSlot {
+  void* ws = nullptr;    // device workspace, allocated by the first call that needs one
+  int* flag = nullptr;   // overflow flag, pinned (the tail of tab_host, or the call's own)
+};
+
 }  // namespace wvp
 
 struct wv_ctx {
@@ -44,13 +52,13 @@ struct wv_ctx {
   unsigned char* tab_dev = nullptr;
   hipEvent_t tab_done[wvp::kTableSlots] = {};
   int tab_next = 0;
-  // encoder: device workspace (allocated by the first call that needs one,
-  // kept until the context is destroyed) and overflow flag (pinned, the tail
-  // of tab_host).  A call holds enc_mu from its launches to its
-  // synchronisation: calls of several threads or streams take turns.
+  // encoder: what a call has to itself while it runs, so that calls of several
+  // threads and streams do not wait for each other.  Up to kEncSlots are kept
+  // until the context is destroyed; a call that finds none idle makes its own
+  // and frees it.
   std::mutex enc_mu;
-  void* enc_ws = nullptr;
-  int* enc_flag = nullptr;
+  wvp::EncSlot enc_idle[wvp::kEncSlots];   // the first enc_n are idle
+  int enc_n = 0;
 };
 
 namespace wvp {

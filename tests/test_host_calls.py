@@ -29,3 +29,11 @@ def test_encoder_call_waits_for_its_kernels_also_after_an_error(tmp_path):
     """The encoder's kernels write the caller's planes and a workspace that
     outlives the call: no call may return while one of them runs."""
     _run("encode_calls", tmp_path)
+
+
+@pytest.mark.parametrize("n", ["2", "4", "7"])
+def test_encoder_calls_of_several_threads_run_side_by_side(tmp_path, n):
+    """Threads with streams of their own on one context: no call waits for
+    another, none shares a workspace or an overflow flag, and what the context
+    keeps is bounded."""
+    _run("encode_calls", tmp_path, n)
