@@ -229,8 +229,8 @@ static wv_status validate_job(const wv_ctx* c, const wv_frame* f, const uint8_t*
 }
 
 // The items of one launch.  Tiles with different level counts differ in work,
-// and every XCD takes a contiguous eighth of the work units: deal the tiles so
-// that each eighth holds the same mix, the tiles with the most levels first.
+// and every XCD takes a contiguous range of the work units: deal the tiles so
+// that each range holds the same mix, the tiles with the most levels first.
 // In tile order neighbours, which the gaze gives the same count, shared an XCD.
 // Foveated at 8192 x 8192, tiles of 512: GOP of 8 in 9/7 332 -> 279 us, in 5/3
 // 101 -> 92; a frame in 9/7 112 -> 91, in 5/3 34 -> 31; a set 192 -> 181 and
@@ -244,7 +244,7 @@ static void copy_items(const Item* src, int n, WorkArgs& a) {
     lo = std::min<int>(lo, src[i].lc);
     hi = std::max<int>(hi, src[i].lc);
   }
-  if (lo == hi || n <= 8) {
+  if (lo == hi || n <= kXcds) {
     std::copy(src, src + n, a.items);
     return;
   }
@@ -255,14 +255,15 @@ static void copy_items(const Item* src, int n, WorkArgs& a) {
     k += c;
   }
   for (int i = 0; i < n; ++i) order[per_level[src[i].lc]++] = i;
-  int at[8], end[8];      // an eighth that starts within a tile starts with its predecessor's last
-  for (int x = 0; x < 8; ++x) {
-    at[x] = (n * x + 7) / 8;
-    end[x] = (n * (x + 1) + 7) / 8;
-  }
+  // the tiles whose first unit lies in each XCD's range
+  const int bpt = a.bx * a.by;
+  int at[kXcds + 1];
+  for (int x = 0; x <= kXcds; ++x) at[x] = (xcd_first(x, a.total) + bpt - 1) / bpt;
+  int end[kXcds];
+  std::copy(at + 1, at + kXcds + 1, end);
   for (int k = 0, pass = 0; k < n; ++pass)
-    for (int i = 0; i < 8 && k < n; ++i) {
-      const int x = pass & 1 ? 7 - i : i;
+    for (int i = 0; i < kXcds && k < n; ++i) {
+      const int x = pass & 1 ? kXcds - 1 - i : i;
       if (at[x] < end[x]) a.items[at[x]++] = src[order[k++]];
     }
 }

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "wv_internal.h"
 #include "wv_lift.h"
 
 namespace wv {
@@ -109,12 +110,10 @@ constexpr int win_max(int B) {
 }
 
 __device__ __forceinline__ int xcd_remap(int b, int g) {
-  // Work groups are dealt to the 8 XCDs round-robin; give each XCD a
+  // Work groups are dealt to the XCDs round-robin; give each XCD a
   // contiguous range of work units so neighbouring blocks of one tile (which
   // share coefficient halos) meet in the same L2.
-  const int X = 8;
-  const int q = g / X, r = g % X, x = b % X, i = b / X;
-  return x * q + min(x, r) + i;
+  return xcd_first(b % kXcds, g) + b / kXcds;
 }
 
 // Ordering of one wave's LDS writes before its own later reads (DS

@@ -8,6 +8,14 @@
 
 namespace wv {
 
+// Grid forms: XCD x takes the work units from xcd_first(x, units) on, a
+// contiguous range (the kernels' xcd_remap).
+constexpr int kXcds = 8;
+__host__ __device__ inline int xcd_first(int x, int units) {
+  const int r = units % kXcds;
+  return x * (units / kXcds) + (x < r ? x : r);
+}
+
 // One viewport decode as the kernels see it (64 bytes).
 struct Job {
   const void* coef[3];   // coefficient planes (tile-major); inter-frame set: band 0

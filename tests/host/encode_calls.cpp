@@ -1,18 +1,15 @@
 // wv_encode_intra's host side against the counting runtime: what a call leaves
 // behind when a launch fails, and calls of several threads on one context.
-#include "hip_stub.h"
-
-#include "wv_api.cpp"
+#define STUB_ENCODE
+#include "api_stub.h"
 
 #include <chrono>
 #include <condition_variable>
-#include <cstdio>
 #include <set>
 #include <thread>
 
 namespace {
 
-wv::Variant block{"block", 64, 64, 256, false, 0, true, 0, -1, 0, -1, -1};
 std::atomic<int> queued{0};      // kernels enqueued and not yet waited for
 bool fail_second = false;        // the launcher's second kernel cannot be launched
 
@@ -38,23 +35,9 @@ hipError_t drain(hipStream_t) {
   return hipSuccess;
 }
 
-int check(bool ok, const char* what) {
-  if (!ok) std::printf("FAILED: %s\n", what);
-  return ok ? 0 : 1;
-}
-
 }  // namespace
 
 namespace wv {
-int fused_variant_count(int, int) { return 1; }
-const Variant* fused_variant(int, int, int v) { return v == 0 ? &block : nullptr; }
-int default_variant(const wv_desc&) { return 0; }
-int few_tiles_variant(const wv_desc&) { return -1; }
-hipError_t launch_fused(int, int, int, const WorkArgs&, int, hipStream_t) { return hipSuccess; }
-hipError_t launch_plain(int, int, const PlainArgs&, hipStream_t) { return hipSuccess; }
-hipError_t launch_strip53_set(int, int, int, const WorkArgs&, hipStream_t) { return hipSuccess; }
-hipError_t launch_strip97_set(int, int, int, const WorkArgs&, hipStream_t) { return hipSuccess; }
-size_t encode_workspace_bytes(int, int, int, int, int) { return 64; }
 hipError_t launch_encode(int, int, int, int, int, int, const void* const*, void* const*, void* ws,
                          int* flag, hipStream_t st) {
   if (meet) {

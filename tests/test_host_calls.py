@@ -37,3 +37,8 @@ def test_encoder_calls_of_several_threads_run_side_by_side(tmp_path, n):
     another, none shares a workspace or an overflow flag, and what the context
     keeps is bounded."""
     _run("encode_calls", tmp_path, n)
+
+
+def test_tiles_of_mixed_levels_are_dealt_over_the_ranges_of_the_xcds(tmp_path):
+    """Every launch size, with one to 32 work units per tile."""
+    _run("deal_items", tmp_path)
