@@ -391,7 +391,7 @@ extern "C" wv_status wv_decode_gop(wv_ctx* c, int32_t n_frames, const wv_frame* 
     WorkArgs a;
     memset(&a, 0, sizeof a);
     fill_geometry(c, var, a);
-      for (int f0 = 0; f0 < n_frames && st == WV_OK; f0 += kArgJobs) {
+    for (int f0 = 0; f0 < n_frames && st == WV_OK; f0 += kArgJobs) {
       const int nf = std::min(kArgJobs, n_frames - f0);
       for (int j = 0; j < nf; ++j) a.jobs[j] = jobs[f0 + j];
       a.n_frames = nf;

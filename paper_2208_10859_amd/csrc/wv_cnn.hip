@@ -958,8 +958,8 @@ using namespace wv::cnn;
 using wvp::fail;
 using wvp::hip_fail;
 
-// weight gradients: at most this many workgroups (the first layer's kernel runs
-// two per CU, the others' one), each writing one row of partial sums
+// weight gradients: at most this many workgroups (one per CU), each writing one
+// row of partial sums
 constexpr int kWgradRows = 256;
 
 constexpr int kMaxGuardTiles = 65536;

@@ -323,7 +323,7 @@ __device__ __forceinline__ void enc_strip(const uint8_t* src, typename LF::CT* d
 struct StripArgs {
   const uint8_t* src[3];
   void* dst[3];
-  void* ws[3];        // approximation after NL levels, or NULL: it is the last level
+  void* ws[3];        // approximation after two levels, or NULL: there are no more
   int n_tiles;
   int rows;           // level 2 rows (4 source rows each) per strip
   int blocks0;        // workgroups of plane 0; planes 1 and 2 follow
@@ -342,7 +342,7 @@ __global__ __launch_bounds__(256) void k_enc_strip(const StripArgs a) {
     const int per = M2 / a.rows, tile = w / per;
     if (tile >= a.n_tiles) return;
     const size_t off = (size_t)tile * P * P;
-    V* ws = a.ws[p] ? (V*)a.ws[p] + off / (NL == 2 ? 16 : 4) : nullptr;
+    V* ws = a.ws[p] ? (V*)a.ws[p] + off / 16 : nullptr;
     enc_strip<LF, c, NL>(a.src[p] + off, (CT*)a.dst[p] + off, ws, (w - tile * per) * a.rows, a.rows, a.q);
   };
   const int b = blockIdx.x;
@@ -442,16 +442,22 @@ __global__ __launch_bounds__(E * 8) void k_enc_tile(const TileArgs a) {
   if (bad) *a.q.overflow = 1;
 }
 
+// e: edges of 8 to 128 from the 8-bit source, of 64 and 128 from the workspace
+// (a quarter of a strip plane's edge).
 template <class LF, class IN>
 hipError_t launch_tile(int e, int planes, int n_tiles, const TileArgs& a, hipStream_t s) {
   const dim3 g(n_tiles, planes);
-  switch (e) {
-    case 128: hipLaunchKernelGGL((k_enc_tile<LF, 128, IN>), g, dim3(1024), 0, s, a); break;
-    case 64: hipLaunchKernelGGL((k_enc_tile<LF, 64, IN>), g, dim3(512), 0, s, a); break;
-    case 32: hipLaunchKernelGGL((k_enc_tile<LF, 32, IN>), g, dim3(256), 0, s, a); break;
-    case 16: hipLaunchKernelGGL((k_enc_tile<LF, 16, IN>), g, dim3(128), 0, s, a); break;
-    case 8: hipLaunchKernelGGL((k_enc_tile<LF, 8, IN>), g, dim3(64), 0, s, a); break;
-    default: return hipErrorInvalidValue;
+  constexpr bool WS = !std::is_same<IN, uint8_t>::value;
+  if (e == 128) {
+    hipLaunchKernelGGL((k_enc_tile<LF, 128, IN>), g, dim3(1024), 0, s, a);
+  } else if (e == 64) {
+    hipLaunchKernelGGL((k_enc_tile<LF, 64, IN>), g, dim3(512), 0, s, a);
+  } else {
+    if constexpr (WS) return hipErrorInvalidValue;
+    else if (e == 32) hipLaunchKernelGGL((k_enc_tile<LF, 32, IN>), g, dim3(256), 0, s, a);
+    else if (e == 16) hipLaunchKernelGGL((k_enc_tile<LF, 16, IN>), g, dim3(128), 0, s, a);
+    else if (e == 8) hipLaunchKernelGGL((k_enc_tile<LF, 8, IN>), g, dim3(64), 0, s, a);
+    else return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
