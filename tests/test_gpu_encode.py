@@ -78,3 +78,32 @@ def test_threads_share_one_context(wavelet):
     for t in threads:
         t.join()
     assert same == [[True] * 20] * 2
+
+
+@pytest.mark.parametrize("tile,levels,grey", CASES)
+def test_float_encoder_differs_at_rounding_ties_only(tile, levels, grey):
+    """9/7: float64 on both sides, so a coefficient of up to 2^10 is off by a few
+    hundred roundings of 2^-53 of it at most, below 1e-10.  An index may differ
+    from the oracle's only where |c| / step + 1/2 lies within 1e-9 of a whole
+    number, and then by one; every other value is the same float.  (The
+    chequerboard's approximation, 127.5 everywhere, is such a tie.)"""
+    from paper_2208_10859_amd import wv
+    dec = wv.Decoder(3 * tile, tile, tile, levels, wv.W97, wv.GRAY8 if grey else wv.YUV420)
+    rng = np.random.default_rng(tile * 10 + levels + 1)
+    src = [rng.integers(0, 256, dec.plane_shape(p), dtype=np.uint8) for p in range(dec.nplanes)]
+    src[0][0] = 255 * (np.indices((tile, tile)).sum(0) & 1)
+    coef = [owv.fwd2d(s, levels, owv.W97) for s in src]
+    assert all(np.abs(c).max() < 1024 for c in coef)
+    dev = [torch.from_numpy(s).cuda() for s in src]
+    for step in (1, 3, 16, 100, 65535):
+        dst = [torch.zeros(dec.plane_shape(p), dtype=dec.coef_dtype, device="cuda") for p in range(dec.nplanes)]
+        dec.encode_intra(dev, dst, step)
+        for g, c in zip(dst, coef):
+            got = g.cpu().numpy()
+            a = np.abs(c) / step + 0.5
+            tie = np.abs(a - np.rint(a)) < 1e-9
+            k = np.where(tie, np.rint(a), np.floor(a))
+            low = np.where(tie, k - 1, k)
+            want = [(step * np.sign(c) * i).astype(np.float32) for i in (k, low)]
+            assert np.all((got == want[0]) | (got == want[1]))
+            assert tie.mean() < 0.1
