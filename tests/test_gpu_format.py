@@ -303,3 +303,36 @@ def test_prefetch_from_store_file_equals_oracle(tmp_path):
             assert err <= TOL97, (s, t, err)
     pfch.close()
     st.close()
+
+
+@pytest.mark.parametrize("tile,levels,tx,ty,wavelet", [
+    (16, 3, 20, 20, W53),     # 389 visible tiles: more than one launch's; luma blocks of 16, chroma of 8
+    (16, 1, 5, 4, W97),
+    (32, 4, 5, 4, W97),       # blocks of 32 and 16, one per plane tile
+    (64, 5, 5, 4, W53),
+    (128, 2, 3, 2, W97),
+    (256, 6, 3, 2, W53),
+])
+def test_rebuild_of_yuv_tiles_of_every_size(tile, levels, tx, ty, wavelet):
+    """One launch rebuilds all planes of a frame, whose block edges and block
+    counts differ: every tile size with mixed level counts, and a viewport of
+    more tiles than a launch takes."""
+    wv, _ = _wv()
+    W, H, n = tx * tile, ty * tile, tx * ty
+    rng = np.random.default_rng(tile + levels)
+    mask = np.ones(n, np.uint8)
+    mask[rng.choice(n, 11 if n > 360 else 2, replace=False)] = 0
+    vis = np.nonzero(mask)[0]
+    lc = rng.integers(0, levels + 1, n).astype(np.uint8)
+    lc[vis[0]] = levels
+    enc, edges = _frame(W, H, tile, levels, wavelet, vis, 500 + tile, 0.05, True)
+    dec = wv.Decoder(W, H, tile, levels, wv.W53 if wavelet == W53 else wv.W97, wv.YUV420)
+    dense, out = _run(dec, enc, mask, lc)
+    _, want, _, want_dense = pf.decode_viewport(enc, edges, mask, levels, wavelet, lc)
+    for p in range(3):
+        assert np.array_equal(dense[p][vis], want_dense[p]), f"plane {p}: rebuilt coefficients differ"
+        assert not dense[p][mask == 0].any(), "tiles outside the mask were written"
+    if wavelet == W53:
+        assert np.array_equal(out, want)
+    else:
+        assert float(np.max(np.abs(out.astype(np.float64) - want))) <= TOL97

@@ -42,3 +42,8 @@ def test_encoder_calls_of_several_threads_run_side_by_side(tmp_path, n):
 def test_tiles_of_mixed_levels_are_dealt_over_the_ranges_of_the_xcds(tmp_path):
     """Every launch size, with one to 32 work units per tile."""
     _run("deal_items", tmp_path)
+
+
+def test_storage_order_by_counting_equals_the_sorted_one(tmp_path):
+    """Every tile edge and level count, and the table of a frame's planes."""
+    _run("storage_order", tmp_path)
