@@ -138,3 +138,28 @@ def test_mixed_level_counts_in_launches_of_any_size(tile, n):
         res.append(outs + list(ref.planes))
     for a, b in zip(*res):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("tile,levels,grey", CASES)
+def test_float_tiles_round_at_random(tile, levels, grey):
+    """9/7: the bound above adds every rounding up with one sign.  Rounding errors
+    of values below 512 are spread over 2^-15, a standard deviation of 2^-15 / sqrt(12)
+    each; the 16 of each level add up as the square root of their number, and the
+    colour conversion adds a chroma error times 1.772 to a luma error, a factor of
+    sqrt(1 + 1.772^2).  The largest of a few million samples lies 5 to 6 such
+    deviations out: 7.5 are allowed in every frame of a chain (the reference is
+    clipped, not transformed: a frame adds the rounding of one sum)."""
+    from paper_2208_10859_amd import wv
+    n_frames = 10
+    gop = Gop(3 * tile, 2 * tile, tile, levels, W97, n_frames, seed=tile * 10 + levels, chroma=not grey)
+    mask = np.array([1, 0, 1, 1, 1, 1], np.uint8)
+    want = gop.oracle([mask] * n_frames, [np.full(6, levels, np.uint8)] * n_frames)
+    dec = wv.Decoder(3 * tile, 2 * tile, tile, levels, wv.W97, wv.GRAY8 if grey else wv.YUV420)
+    frames = [([torch.from_numpy(p).cuda() for p in f["coeffs"]], f["intra"], f["step"]) for f in gop.frames]
+    ref = wv.Reference(dec)
+    outs = [torch.empty(dec.out_shape(5), dtype=dec.sample_dtype, device="cuda") for _ in range(n_frames)]
+    dec.decode_gop(frames, 0, mask, ref, outs)
+    tol = 7.5 * 2.0 ** -15 * np.sqrt(16 * levels / 12) * (1.0 if grey else np.sqrt(1 + 1.772 ** 2))
+    for t in range(n_frames):
+        err = float(np.max(np.abs(outs[t].cpu().numpy().astype(np.float64) - want[t][1])))
+        assert err <= tol, (t, err, tol)
