@@ -382,7 +382,7 @@ def config1_latency(seed, steps=200, warmup=20):
     graph_us = (time.perf_counter() - t0) / steps * 1e6
     st = launch_stats(t)
     return {"gpu_us_p50": st["p50_us"], "gpu_us_min": st["min_us"], "eager_us_per_call": eager_us,
-            "graph_us_per_call": graph_us, "calls": steps, "variant": dec.variants()[dec.variant],
+            "graph_us_per_call": graph_us, "calls": steps, "variant": "untuned (the call's size chooses)",
             "bytes_per_call": 512 * 512 * 3,
             "note": "latency-bound (0.8 MB per call): no roofline fraction"}
 

@@ -83,7 +83,7 @@ __device__ __forceinline__ uint32_t pk_bf16(float a, float b) {
 // There, 32 dy channels: 21 us; as two kernels 27.8 us (14.9 weights, 12.9
 // data), 3 dy channels: 14.2 us against 10.4 + 9.7.  With every wave doing both
 // parts in turn the registers ran out (23 and 14.9 us).  FIRST:
-// 25 us; with a kernel of its own for the first layer 20.8 + 7.5.  Weight gradients
+// 22 us; with a kernel of its own for the first layer 20.8 + 7.5.  Weight gradients
 // from transposed copies written to LDS a word at a time took 19.4 us.
 //   DYC: dy channels in memory (32, or 4 of which 3 are real).
 //   img, part0, width0: FIRST: the image, rows of the first layer's sums.

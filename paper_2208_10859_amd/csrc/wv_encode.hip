@@ -19,8 +19,9 @@
 // frame, 58 us at a copy's rate; the strip kernel takes 71 us, 4.4 TB/s), the
 // float64 arithmetic for 9/7 (4096 x 4096: 47 us against 24).  One pass per
 // level and direction through a workspace of every sample, allocated and freed
-// by each call, moved about 30 (60) bytes per sample; whole calls: 1598 -> 105 us
-// (5/3, 8192 x 8192, five levels), 4538 -> 82 us (9/7, 4096 x 4096).
+// by each call, moved about 30 (60) bytes per sample; whole calls: 1598 -> 107 us
+// (5/3, 8192 x 8192, five levels), 2700 to 4560 (the allocations varied) -> 80 us
+// (9/7, 4096 x 4096).
 #include <algorithm>
 #include <type_traits>
 

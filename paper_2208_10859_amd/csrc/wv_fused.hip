@@ -431,11 +431,19 @@ int default_variant(const wv_desc& d) {
   return -1;
 }
 
-// Grey 5/3 frames of 512-sample tiles: up to 24 tiles the 32-row strips leave
-// CUs idle and the 16-row chain strips are faster (us, three levels: a frame of
-// 1 / 6 / 24 tiles 7.8 -> 6.4, 7.8 -> 6.8, 9.9 -> 9.6, a GOP of 8 39.7 -> 30.8,
-// 42.8 -> 32.4, 56.8 -> 49.5); beyond, they are slower (120 tiles: 27.1 against
-// 29.9).  9/7: 10.7 / 10.6, 12.3 / 12.6, and 15.8 / 18.4 at 16 tiles, so never.
+// Grey 5/3 frames of 512-sample tiles: up to 24 tiles the 32-row strips (16 units
+// a tile, three to a CU) fill half of the chip at most and the 16-row chain strips
+// are faster; from 28 on they are not.  GPU time, 32-row -> 16-row (us):
+//                   1 tile         8 tiles        24 tiles       28 tiles       48 tiles       120 tiles
+//   frame, L = 3    6.2 -> 5.1     6.6 -> 5.6     8.6 -> 8.3     8.7 -> 9.4    11.8 -> 14.9   25.4 -> 27.9
+//          L = 4    6.8 -> 5.6     7.2 -> 6.1     9.2 -> 8.7     9.3 -> 9.8    12.5 -> 16.1   26.5 -> 30.1
+//          L = 5    7.3 -> 6.1     7.8 -> 6.7     9.7 -> 9.4     9.9 -> 10.5   13.1 -> 17.3   27.4 -> 32.6
+//   GOP 8, L = 3   38.7 -> 29.8   44.5 -> 33.7   55.4 -> 47.7   55.7 -> 55.7   82.0 -> 103.5  194.5 -> 209.1
+//          L = 4   43.3 -> 33.9   49.8 -> 38.6   59.3 -> 51.8   60.1 -> 58.6   75.3 -> 97.4   206.0 -> 227.3
+//          L = 5   47.5 -> 37.9   55.3 -> 43.5   63.0 -> 56.5   62.9 -> 61.5   78.5 -> 107.5  215.9 -> 245.7
+// A call from Python takes about 12 us of host time, which hides a frame's gain
+// but for graphs and threads; a GOP's shows in the call.  9/7: 10.7 / 10.6,
+// 12.3 / 12.6, and 15.8 / 18.4 at 16 tiles, so never.
 int few_tiles_variant(const wv_desc& d) {
   if (d.format != WV_GRAY8 || d.wavelet != WV_W53) return -1;
   for (int v = 0; v < kNumVariants; ++v) {

@@ -11,11 +11,13 @@
 // colour and output on four adjacent samples per thread.  The reference stays
 // in registers between the frames of a GOP and is read and written only at its
 // ends.
-// What bounds it: instruction issue (two wavefronts per SIMD with few tiles,
-// about 5000 instructions for four frames of a 64-sample tile), then latency.
+// What bounds it: a workgroup per tile, so fewer tiles than CUs leave the others
+// idle (100 of 256 CUs in the case below); on a CU instruction issue (two
+// wavefronts per SIMD, about 5000 instructions for four frames of a 64-sample
+// tile), then latency.
 // GOP of 8 frames, 1920 x 1920 YUV420, 64-sample tiles, 5/3, four levels,
-// 110 x 110 degree viewport: 40.6 us a call (block kernel, a launch per frame:
-// 256).
+// 110 x 110 degree viewport (100 tiles): 39 us a call (block kernel, a launch per
+// frame: 256).
 #include <type_traits>
 
 #include "wv_fused_common.h"
