@@ -273,7 +273,7 @@ wv_status wv_autotune(wv_ctx* ctx, int32_t n_visible, int32_t reps, hipStream_t 
                       int32_t* best_variant);
 
 /* Number of fused variants, and the one in use; select one by index.  Until
- * one is selected or tuned, calls of few visible tiles may run in another
+ * one is selected or tuned, calls of some numbers of visible tiles run in another
  * variant that is faster for them; then the chosen one runs for every call. */
 int32_t wv_variant_count(const wv_ctx* ctx);
 wv_status wv_get_variant(const wv_ctx* ctx, int32_t* variant);

@@ -109,7 +109,7 @@ wv_status wv_create(wv_ctx** out, const wv_desc* desc) {
     return st;
   }
   c->variant = default_variant(c->d);
-  c->few_variant = few_tiles_variant(c->d);
+  c->alt_variant = alternative_variant(c->d);
   if (c->variant < 0) {
     wv_destroy(c);
     return fail(WV_EUNSUPPORTED, "no fused variant fits tile %d", desc->tile);
@@ -167,7 +167,7 @@ wv_status wv_set_variant(wv_ctx* c, int32_t v) {
   if (!var) return fail(WV_EINVAL, "variant %d out of range", v);
   if (!variant_fits(c->d, var)) return fail(WV_EUNSUPPORTED, "variant %s does not fit tile %d", var->name, c->d.tile);
   c->variant = v;
-  c->few_variant = -1;   // the caller's choice holds for every call
+  c->alt_variant = -1;   // the caller's choice holds for every call
   return WV_OK;
 }
 
@@ -290,9 +290,48 @@ void wvp::fill_geometry(const wv_ctx* c, const Variant* var, WorkArgs& a) {
   a.items_dev = nullptr;
 }
 
-// The variant of a call of n visible tiles.
-static int call_variant(const wv_ctx* c, size_t n) {
-  return c->few_variant >= 0 && n <= (size_t)kFewTiles ? c->few_variant : c->variant;
+// The variant of a call: the context's, or its alternative where that is the
+// better one.  There is one for 5/3 tiles of 512 until the caller chooses: grey
+// contexts start with the 32-row strips, YUV420 ones with the 16-row chain strips.
+// Grey frames and GOPs: up to 24 tiles the 32-row strips (16 units
+// a tile, three to a CU) fill half of the chip at most and the 16-row chain strips
+// are faster; from 28 on they are not.  GPU time, 32-row -> 16-row (us):
+//                   1 tile         8 tiles        24 tiles       28 tiles       48 tiles       120 tiles
+//   frame, L = 3    6.2 -> 5.1     6.6 -> 5.6     8.6 -> 8.3     8.7 -> 9.4    11.8 -> 14.9   25.4 -> 27.9
+//          L = 4    6.8 -> 5.6     7.2 -> 6.1     9.2 -> 8.7     9.3 -> 9.8    12.5 -> 16.1   26.5 -> 30.1
+//          L = 5    7.3 -> 6.1     7.8 -> 6.7     9.7 -> 9.4     9.9 -> 10.5   13.1 -> 17.3   27.4 -> 32.6
+//   GOP 8, L = 3   38.7 -> 29.8   44.5 -> 33.7   55.4 -> 47.7   55.7 -> 55.7   82.0 -> 103.5  194.5 -> 209.1
+//          L = 4   43.3 -> 33.9   49.8 -> 38.6   59.3 -> 51.8   60.1 -> 58.6   75.3 -> 97.4   206.0 -> 227.3
+//          L = 5   47.5 -> 37.9   55.3 -> 43.5   63.0 -> 56.5   62.9 -> 61.5   78.5 -> 107.5  215.9 -> 245.7
+// A call from Python takes about 12 us of host time, which hides a frame's gain
+// but for graphs and threads; a GOP's shows in the call.  9/7: 10.7 / 10.6,
+// 12.3 / 12.6, and 15.8 / 18.4 at 16 tiles, so never.
+// YUV420: the chip holds five 16-row units per CU (of set frames four), which are
+// 40 (32) tiles, or three 32-row units, 48 tiles.  A GOP of 41 to 48 tiles is one
+// round of the larger units and two of the smaller.  GPU time of a GOP of 8, 32-row
+// / 16-row, coefficients from memory (us):
+//             40 tiles         41             44             48             49             96
+//   L = 5   175.9 / 134.3  177.5 / 185.9  177.6 / 190.8  182.1 / 199.8  273.8 / 201.0  359.7 / 345.2
+//   L = 4   170.1 / 130.8  170.3 / 171.7  172.3 / 180.5  174.7 / 192.7  261.1 / 194.6  344.9 / 331.2
+//   L = 3   159.2 / 123.0  159.3 / 155.5  161.0 / 164.4  165.6 / 173.5  236.4 / 175.7  324.4 / 301.3
+// Single frames gain from the smaller units at every size (44 tiles, L = 5: intra
+// 28.5 / 28.5, residual 31.4 / 28.8).
+// Sets: the larger units are the better ones when their last round is more than
+// two thirds full, for one, two or four frames alike (four frames, us):
+//             32 tiles         33             40             48             49             80             96            112            144            160
+//   L = 5   87.2 / 82.3   103.1 / 104.6  101.6 / 116.8  115.5 / 139.0  161.8 / 141.5  207.8 / 211.0  229.1 / 243.2  301.6 / 288.2  341.5 / 360.0  404.0 / 395.6
+//   L = 3   79.0 / 75.4    95.2 / 93.3    94.4 / 103.6  108.2 / 123.0  147.1 / 126.2  192.2 / 187.5  217.1 / 219.6  277.0 / 257.5  318.6 / 326.7  373.4 / 362.9
+static int call_variant(const wv_ctx* c, size_t tiles, int n_frames, bool set) {
+  if (c->alt_variant < 0 || tiles == 0) return c->variant;
+  const size_t cu = c->n_cu, round = std::max<size_t>(3 * cu / 16, 1);   // tiles of a round of 32-row units
+  bool alt;
+  if (c->d.format == WV_GRAY8)
+    alt = !set && tiles * 32 <= 3 * cu;
+  else if (set)
+    alt = 3 * ((tiles - 1) % round) >= 2 * round;
+  else
+    alt = n_frames > 1 && tiles * 32 > 5 * cu && tiles <= round;
+  return alt ? c->alt_variant : c->variant;
 }
 
 // Launch a job list through kernel arguments, in chunks of kArgItems items.
@@ -349,7 +388,7 @@ extern "C" wv_status wv_decode_viewport(wv_ctx* c, const wv_frame* f, const uint
   if (c->path == WV_PATH_PLAIN)
     st = launch_plain_items(c, job, plan.items, s);
   else
-    st = launch_arg_chunks(c, call_variant(c, plan.items.size()), &job, 1, plan.items, s);
+    st = launch_arg_chunks(c, call_variant(c, plan.items.size(), 1, false), &job, 1, plan.items, s);
   if (st != WV_OK) return st;
   for (const Item& it : plan.items) ref->tile_stamp[it.tile] = f->frame_index;
   return WV_OK;
@@ -382,7 +421,7 @@ extern "C" wv_status wv_decode_gop(wv_ctx* c, int32_t n_frames, const wv_frame* 
     jobs[f] = make_job(c, &frames[f], ref, out);
   }
   if (plan.items.empty()) return WV_OK;
-  const int variant = call_variant(c, plan.items.size());
+  const int variant = call_variant(c, plan.items.size(), n_frames, false);
   const Variant* var = fused_variant(c->d.wavelet, c->d.format, variant);
   wv_status st = WV_OK;
   if (c->path == WV_PATH_FUSED && var->kind >= 2) {
@@ -443,8 +482,10 @@ extern "C" wv_status wv_decode_set(wv_ctx* c, const wv_set* set, int32_t t0, int
     for (int b = 0; b < set->n; ++b)
       if (set->qstep[b] < 1 || set->qstep[b] > 65535)
         return fail(WV_EINVAL, "wv_decode_set: qstep[%d] = %d outside 1..65535", b, set->qstep[b]);
-  // the context's variant if it is a row strip, else the first row strip that fits
-  const Variant* var = fused_variant(c->d.wavelet, c->d.format, c->variant);
+  size_t n_visible = 0;
+  for (int t = 0; t < c->n_tiles; ++t) n_visible += mask[t] != 0;
+  // the call's variant if it is a row strip, else the first row strip that fits
+  const Variant* var = fused_variant(c->d.wavelet, c->d.format, call_variant(c, n_visible, n_frames, true));
   if (!var || var->kind != 2 || var->bw != 512) {
     var = nullptr;
     const int nv = fused_variant_count(c->d.wavelet, c->d.format);
@@ -534,7 +575,7 @@ extern "C" wv_status wv_decode_batch(int32_t n_jobs, const wv_job* jobs, hipStre
   }
   if ((int)items.size() > kTableItems) return fail(WV_EINVAL, "at most %d visible tiles per batch", kTableItems);
   if (!items.empty()) {
-    const int variant = call_variant(c0, items.size());
+    const int variant = call_variant(c0, items.size(), 1, false);
     const Variant* var = fused_variant(c0->d.wavelet, c0->d.format, variant);
     if (n_jobs <= kArgJobs && (int)items.size() <= kArgItems) {
       wv_status st = launch_arg_chunks(c0, variant, table.data(), n_jobs, items, s);
@@ -687,7 +728,7 @@ extern "C" wv_status wv_autotune(wv_ctx* c, int32_t n_visible, int32_t reps, hip
     }
     if (best >= 0) {
       c->variant = best;
-      c->few_variant = -1;
+      c->alt_variant = -1;
     }
   }
   if (t0) hipEventDestroy(t0);

@@ -44,7 +44,7 @@ struct wv_ctx {
   int nplanes = 1;
   int path = WV_PATH_FUSED;
   int variant = 0;
-  int few_variant = -1;            // for calls of few tiles, until the caller chooses a variant (-1: none)
+  int alt_variant = -1;            // for calls of some sizes, until the caller chooses a variant (-1: none)
   uint32_t* counter = nullptr;     // persistent-queue counters (device, 2 words)
   void* plain_ws = nullptr;        // plain-path workspace (device)
   // batch tables: pinned staging + device copy, double-buffered

@@ -419,7 +419,8 @@ const Variant* fused_variant(int, int, int v) {
 // and 23.0 -> 21.6, its GOP of 8 88.3 -> 52.4 and 160.9 -> 148.3; a 9/7 frame
 // 22.0 -> 15.2 and 80.3 -> 53.9, its GOP 159.8 -> 104.6 and 684.4 -> 492.4; 256
 // tiles: 147.3 -> 129.2 and 509.6 -> 368.1.  Grey frames have no chroma chains to
-// run beside the luma one: the 32-row form stays, but for few tiles (below).
+// run beside the luma one: the 32-row form stays.  Some call sizes take the
+// other form (alternative_variant).
 int default_variant(const wv_desc& d) {
   for (int v = 0; v < kNumVariants; ++v) {
     const Variant& var = kVariants[v];
@@ -431,24 +432,14 @@ int default_variant(const wv_desc& d) {
   return -1;
 }
 
-// Grey 5/3 frames of 512-sample tiles: up to 24 tiles the 32-row strips (16 units
-// a tile, three to a CU) fill half of the chip at most and the 16-row chain strips
-// are faster; from 28 on they are not.  GPU time, 32-row -> 16-row (us):
-//                   1 tile         8 tiles        24 tiles       28 tiles       48 tiles       120 tiles
-//   frame, L = 3    6.2 -> 5.1     6.6 -> 5.6     8.6 -> 8.3     8.7 -> 9.4    11.8 -> 14.9   25.4 -> 27.9
-//          L = 4    6.8 -> 5.6     7.2 -> 6.1     9.2 -> 8.7     9.3 -> 9.8    12.5 -> 16.1   26.5 -> 30.1
-//          L = 5    7.3 -> 6.1     7.8 -> 6.7     9.7 -> 9.4     9.9 -> 10.5   13.1 -> 17.3   27.4 -> 32.6
-//   GOP 8, L = 3   38.7 -> 29.8   44.5 -> 33.7   55.4 -> 47.7   55.7 -> 55.7   82.0 -> 103.5  194.5 -> 209.1
-//          L = 4   43.3 -> 33.9   49.8 -> 38.6   59.3 -> 51.8   60.1 -> 58.6   75.3 -> 97.4   206.0 -> 227.3
-//          L = 5   47.5 -> 37.9   55.3 -> 43.5   63.0 -> 56.5   62.9 -> 61.5   78.5 -> 107.5  215.9 -> 245.7
-// A call from Python takes about 12 us of host time, which hides a frame's gain
-// but for graphs and threads; a GOP's shows in the call.  9/7: 10.7 / 10.6,
-// 12.3 / 12.6, and 15.8 / 18.4 at 16 tiles, so never.
-int few_tiles_variant(const wv_desc& d) {
-  if (d.format != WV_GRAY8 || d.wavelet != WV_W53) return -1;
+// 5/3, tiles of 512: the other of the 32-row and 16-row strips, which is faster
+// for some numbers of tiles (call_variant).
+int alternative_variant(const wv_desc& d) {
+  if (d.wavelet != WV_W53) return -1;
+  const int shape = d.format == WV_GRAY8 ? 4 : 0;
   for (int v = 0; v < kNumVariants; ++v) {
     const Variant& var = kVariants[v];
-    if (var.kind == 2 && var.bw == 512 && var.shape == 4 && !var.persistent && wvp::variant_fits(d, &var)) return v;
+    if (var.kind == 2 && var.bw == 512 && var.shape == shape && !var.persistent && wvp::variant_fits(d, &var)) return v;
   }
   return -1;
 }

@@ -101,8 +101,7 @@ struct Variant {
 int fused_variant_count(int wavelet, int format);
 const Variant* fused_variant(int wavelet, int format, int v);
 int default_variant(const wv_desc& d);   // -1: none fits
-constexpr int kFewTiles = 24;
-int few_tiles_variant(const wv_desc& d); // the better one for calls of up to kFewTiles tiles, or -1
+int alternative_variant(const wv_desc& d);   // the better one for calls of some sizes, or -1
 hipError_t launch_fused(int wavelet, int format, int v, const WorkArgs& a, int n_cu,
                         hipStream_t s);
 hipError_t launch_fast53(int format, int shape, int L, bool pers, const WorkArgs& a, int n_cu,

@@ -463,3 +463,33 @@ def test_gpu_encoder_matches_oracle(wavelet, levels):
             # float64 forward on both sides; a rounding tie may move one step
             diff = np.abs(got.astype(np.float64) - want)
             assert np.mean(diff > 0) < 1e-4 and diff.max() <= gop.intra_step
+
+
+@pytest.mark.parametrize("n_vis", [32, 33, 40, 41, 48, 49])
+def test_yuv_calls_on_both_sides_of_the_strip_rule(n_vis):
+    """5/3 GOPs and sets on 512-sample tiles take other strips for some numbers of
+    tiles until the caller chooses a variant: the bytes are those of a chosen one."""
+    from paper_2208_10859_amd import wv
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n_vis)
+    res = []
+    dec = wv.Decoder(7 * 512, 7 * 512, 512, 3, wv.W53, wv.YUV420)
+    gop = [[torch.randint(-40, 40, dec.plane_shape(p), generator=gen, device="cuda", dtype=torch.int16)
+            for p in range(3)] for _ in range(2)]
+    bands = [torch.randint(-20, 20, dec.set_shape(4, p), generator=gen, device="cuda", dtype=torch.int16)
+             for p in range(3)]
+    mask = np.zeros(49, np.uint8)
+    mask[:n_vis] = 1
+    for pick in (None, "strip_r32_w4_L3_grid", "strip_r16_w4_L3_chain_grid"):
+        d = wv.Decoder(7 * 512, 7 * 512, 512, 3, wv.W53, wv.YUV420)
+        if pick is not None:
+            d.variant = d.variants().index(pick)
+        ref = wv.Reference(d)
+        outs = [torch.empty(d.out_shape(n_vis), dtype=torch.uint8, device="cuda") for _ in range(6)]
+        d.decode_gop([(gop[0], True, 3), (gop[1], False, 1)], 0, mask, ref, outs[:2])
+        d.decode_set(bands, 4, (3, 2, 1, 1), 0, mask, outs[2:])
+        torch.cuda.synchronize()
+        res.append(outs + list(ref.planes))
+    for r in res[1:]:
+        for a, b in zip(r, res[0]):
+            assert torch.equal(a, b)

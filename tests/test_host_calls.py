@@ -47,3 +47,10 @@ def test_tiles_of_mixed_levels_are_dealt_over_the_ranges_of_the_xcds(tmp_path):
 def test_storage_order_by_counting_equals_the_sorted_one(tmp_path):
     """Every tile edge and level count, and the table of a frame's planes."""
     _run("storage_order", tmp_path)
+
+
+def test_calls_take_the_strips_that_suit_their_number_of_tiles(tmp_path):
+    """GOPs of 41 to 48 tiles and sets whose last round of 32-row strips is more
+    than two thirds full run in those, other YUV420 calls in the 16-row ones; a
+    chosen variant holds for every call."""
+    _run("call_variant", tmp_path)
