@@ -1272,6 +1272,25 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
     lout.refv = &lkeep;
   }
 
+  // The reference rows of the finest luma rows: zero for an intra frame, from
+  // memory, or kept.  With the three ways in one place the compiler waited for
+  // the loads at once and copied them to the kept registers; with the zeros at
+  // the start of the frame (ZFIRST) it loads into those (9/7 grey, 32 rows: 236 -> 184
+  // registers).  A residual frame of one grey tile 10.7 -> 10.3 us, 12 tiles of
+  // YUV420 in 32-row strips 2 % faster; the 16-row YUV420 strips (GOPs of four 3 %)
+  // and the packed 5/3 rows (1 %) are better with the former.
+  constexpr bool ZFIRST = KEEPY && sizeof(RT) == 4 && (!YUV || R == 32);
+  if constexpr (ZFIRST)
+    if (intra) lkeep.template zero<K1>();
+  auto luma_ref = [&]() __attribute__((always_inline)) {
+    if constexpr (ZFIRST) {
+      if (first && !intra) prefetch_ref<K1>(lout.ref, lout.lo, P, j0y, lkeep);
+    } else {
+      if (intra) lkeep.template zero<K1>();
+      else if (!KEEPY || first) prefetch_ref<K1>(lout.ref, lout.lo, P, j0y, lkeep);
+    }
+  };
+
   if constexpr (SCHED == 1) {
     // the finest luma rows of this wave (the last phase of every schedule)
     // 5/3 stored frames: its loads go out at the start of the frame and
@@ -1286,8 +1305,7 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
     };
     auto luma1 = [&]() __attribute__((always_inline)) {
       if constexpr (!EARLY) luma1_load();
-      if (intra) lkeep.template zero<K1>();
-      else if (!KEEPY || first) prefetch_ref<K1>(lout.ref, lout.lo, P, j0y, lkeep);
+      luma_ref();
       const typename LF::V* sw = nullptr;
       int sa = 0, srows = 1;
       if constexpr (L > 1) {
@@ -1389,8 +1407,7 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
               seg_load<LF, P, P, K1, L == 1, true>(py.coef, lane, j0y, ly);
             else
               seg_load<LF, P, P, K1, L == 1, false>(py.coef, lane, j0y, ly);
-            if (intra) lkeep.template zero<K1>();
-            else if (!KEEPY || first) prefetch_ref<K1>(lout.ref, lout.lo, P, j0y, lkeep);
+            luma_ref();
             const typename LF::V* sw = nullptr;
             int sa = 0, srows = 1;
             if constexpr (L > 1) {

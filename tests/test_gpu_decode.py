@@ -493,3 +493,55 @@ def test_yuv_calls_on_both_sides_of_the_strip_rule(n_vis):
     for r in res[1:]:
         for a, b in zip(r, res[0]):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("wavelet", [W53, W97])
+@pytest.mark.parametrize("tile,levels,grey", [(512, 3, True), (512, 4, False), (256, 3, True), (256, 3, False),
+                                              (128, 3, False), (64, 3, True)])
+def test_gop_with_intra_frames_inside_equals_its_frames(tile, levels, grey, wavelet):
+    """A GOP call in which residual and intra frames alternate, from a residual
+    first frame on: the reference kept on chip between the frames is dropped at
+    each intra frame.  Every variant gives the bytes of its frame-by-frame form, but
+    in 9/7 the whole-tile kernel takes four frames or one through code of its own,
+    whose roundings differ (each is within 7.5 standard deviations of the exact value,
+    4.6e-4 for three grey levels), and the block variants, which have only the one
+    form, let two threads compute a row."""
+    from paper_2208_10859_amd import wv
+    dec = wv.Decoder(3 * tile, tile, tile, levels, wv.W53 if wavelet == W53 else wv.W97,
+                     wv.GRAY8 if grey else wv.YUV420)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(tile + levels)
+    frames = []
+    for t, (intra, step, amp) in enumerate([(True, 4, 30), (False, 1, 6), (False, 1, 6), (True, 4, 30), (False, 1, 6),
+                                            (True, 4, 30), (True, 4, 30), (False, 1, 6), (False, 1, 6)]):
+        planes = [torch.randint(-amp, amp + 1, dec.plane_shape(p), generator=gen, device="cuda").to(dec.coef_dtype)
+                  for p in range(dec.nplanes)]
+        frames.append((planes, intra, step))
+    mask = np.array([1, 0, 1], np.uint8)
+    fitting = 0
+    for v, name in enumerate(dec.variants()):
+        try:
+            dec.variant = v
+        except wv.WvError:
+            continue
+        if wavelet == W97 and not name.startswith(("strip", "tile")):
+            continue
+        fitting += 1
+        res = []
+        for gop in (False, True):
+            ref = wv.Reference(dec)
+            outs = [torch.empty(dec.out_shape(2), dtype=dec.sample_dtype, device="cuda") for _ in frames]
+            dec.decode_viewport(frames[0][0], 0, True, 4, mask, ref, outs[0])
+            if gop:
+                dec.decode_gop(frames[1:], 1, mask, ref, outs[1:])
+            else:
+                for t, (planes, intra, step) in enumerate(frames[1:], 1):
+                    dec.decode_viewport(planes, t, intra, step, mask, ref, outs[t])
+            torch.cuda.synchronize()
+            res.append(outs + list(ref.planes))
+        for a, b in zip(*res):
+            if wavelet == W97 and name.startswith("tile"):
+                assert (a - b).abs().max() <= 2 * 4.6e-4
+            else:
+                assert torch.equal(a, b), name
+    assert fitting
