@@ -417,8 +417,8 @@ const Variant* fused_variant(int, int, int v) {
 // resident units per CU hide each other's latency, against the 32-row phased
 // ones that come first (us, five levels, 1 and 36 tiles): a 5/3 frame 13.7 -> 9.0
 // and 23.0 -> 21.6, its GOP of 8 88.3 -> 52.4 and 160.9 -> 148.3; a 9/7 frame
-// 22.0 -> 15.2 and 80.3 -> 53.9, its GOP 159.8 -> 104.6 and 684.4 -> 492.4; 256
-// tiles: 147.3 -> 129.2 and 509.6 -> 368.1.  Grey frames have no chroma chains to
+// 22.0 -> 15.2 and 80.3 -> 53.9, its GOP 159.8 -> 104.6 and 684.4 -> 492.4; a frame
+// of 256 tiles, 5/3 and 9/7: 147.3 -> 129.2 and 509.6 -> 368.1.  Grey frames have no chroma chains to
 // run beside the luma one: the 32-row form stays.  Some call sizes take the
 // other form (alternative_variant).
 int default_variant(const wv_desc& d) {

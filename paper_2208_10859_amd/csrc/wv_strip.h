@@ -738,7 +738,11 @@ struct LumaOut {
   // 16 bytes, and plain stores are the better ones there (a 9/7 frame 60.6
   // against 62.8 us, a foveated GOP 332 against 357).  Elsewhere, streaming
   // against plain: 9/7 GOPs of 256-sample tiles 141 / 181, of 128-sample ones
-  // 193 / 234, a 9/7 set of four 228 / 269, grey GOPs 115 / 120 us.
+  // 193 / 234, a 9/7 set of four 228 / 269, grey GOPs 115 / 120 us.  Single grey 9/7
+  // frames of 512-sample tiles, coefficients from memory: 8 tiles 12.5 / 14.4, 24
+  // 20.5 / 21.8, 48 38.6 / 40.1, but 32 (every CU full at once) 29.7 / 27.2 and 64
+  // 53.6 / 51.9; a frame decoded into the same cached output again and again, 32
+  // tiles: 29.6 / 23.3.
   static constexpr bool NT = !(sizeof(RT) == 4 && FMT == WV_YUV420 && C == 8 && WREF);
   __device__ __forceinline__ static void st_out(WV_G RT* p, const V (&v)[C]) {
     if constexpr (NT) st_px_nt<C>(p, v);
@@ -1276,9 +1280,10 @@ __device__ __forceinline__ void strip_unit(Smem<LF, FMT, P, L, R, SCHED>& sm, co
   // memory, or kept.  With the three ways in one place the compiler waited for
   // the loads at once and copied them to the kept registers; with the zeros at
   // the start of the frame (ZFIRST) it loads into those (9/7 grey, 32 rows: 236 -> 184
-  // registers).  A residual frame of one grey tile 10.7 -> 10.3 us, 12 tiles of
-  // YUV420 in 32-row strips 2 % faster; the 16-row YUV420 strips (GOPs of four 3 %)
-  // and the packed 5/3 rows (1 %) are better with the former.
+  // registers).  Grey 9/7, a residual frame of one tile 10.4 -> 9.8 us (five levels 12.2
+  // -> 11.7), a GOP of 8 of 20 tiles 88.4 -> 84.8; YUV420 in 32-row strips, 100 tiles and
+  // four levels, 235 -> 223 and 1460 -> 1390.  The 16-row YUV420 strips (GOPs of four
+  // 3 %) and the packed 5/3 rows (1 %) are better with the former.
   constexpr bool ZFIRST = KEEPY && sizeof(RT) == 4 && (!YUV || R == 32);
   if constexpr (ZFIRST)
     if (intra) lkeep.template zero<K1>();
