@@ -30,7 +30,8 @@
  *    return; completion is stream-ordered.  No call throws; every call
  *    returns a wv_status.  On any error nothing has been enqueued and no
  *    caller-visible state (stamps included) has changed.
- *  - A context is used by one host thread at a time.
+ *  - A context is used by one host thread at a time, but for wv_encode_intra,
+ *    which several may call at once.
  */
 #ifndef WV_H
 #define WV_H
